@@ -674,6 +674,7 @@ struct mjh_batch {
   size_t lds_bytes = 0;
   bool rk4 = false;  // some group integrates by fourth-order Runge-Kutta
   bool cone = false; // some group's model has elliptic cones
+  RegShape reg;      // kernels with register-resident solves (nb = 0: the others)
   bool dirty = true;       // launch shape or world counts changed: rebuild the tables
   bool ptrs_dirty = false; // only bound pointers changed: rewrite d_groups in place
   hipGraph_t graph = nullptr;
@@ -784,6 +785,23 @@ static mjh_status sync_tables(mjh_batch* b) {
     if (gr.nworld > 0 && ctx->models[gr.model]->dm.rk4) b->rk4 = true;
     if (gr.nworld > 0 && ctx->models[gr.model]->dm.cone) b->cone = true;
   }
+  // register-resident solves where every group has them: one shape, or a mix of the shapes
+  // that the mixed kernel holds
+  b->reg = RegShape();
+  bool first = true, same = true, mix = !b->rk4;
+  for (const GroupRec& gr : b->groups) {
+    if (gr.nworld == 0) continue;
+    const RegShape r = reg_shape(ctx->models[gr.model]->dm, gr.team);
+    mix = mix && mix_shape(r);
+    same = same && (first || (r.team == b->reg.team && r.nb == b->reg.nb));
+    if (first) b->reg = r;
+    first = false;
+  }
+  if (!same) {
+    b->reg = RegShape();
+    if (mix) b->reg.nb = 28;
+  }
+  if (b->reg.nb) b->block = (b->block + 63) & ~63;  // whole wavefronts (team_of)
   b->dirty = false;
   b->ptrs_dirty = false;
   if (b->graph_exec) { (void)hipGraphExecDestroy(b->graph_exec); b->graph_exec = nullptr; }
@@ -991,7 +1009,7 @@ mjh_status mjh_step(mjh_batch* b, int32_t nstep, void* stream) {
   if (st != MJH_OK) return st;
   if (nstep == 0 || b->ntask == 0) return MJH_OK;
   MJH_HIP(launch_step(b->d_groups, b->d_tasks, b->ntask, nstep, b->block, b->lds_bytes,
-                      b->tab_words, b->rk4, b->cone, static_cast<hipStream_t>(stream)));
+                      b->tab_words, b->rk4, b->cone, b->reg, static_cast<hipStream_t>(stream)));
   return MJH_OK;
 }
 
@@ -1039,7 +1057,7 @@ mjh_status mjh_env_step(mjh_batch* b, int32_t nenv, int32_t nsub, const float* a
   E.last_action = last_action; E.obs = obs; E.reward = reward; E.done = done;
   E.ndr = ndr; E.dr = params; E.noise = obs_noise;
   MJH_HIP(launch_env(b->d_groups, b->d_tasks, b->ntask, E, b->block, lds, b->tab_words, ap_words,
-                     b->rk4, static_cast<hipStream_t>(stream)));
+                     b->rk4, b->reg, static_cast<hipStream_t>(stream)));
   return MJH_OK;
 }
 
@@ -1056,7 +1074,7 @@ mjh_status mjh_graph_capture(mjh_batch* b, int32_t nstep, void* stream) {
   if (b->graph) { (void)hipGraphDestroy(b->graph); b->graph = nullptr; }
   MJH_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
   hipError_t le = launch_step(b->d_groups, b->d_tasks, b->ntask, nstep, b->block, b->lds_bytes,
-                              b->tab_words, b->rk4, b->cone, s);
+                              b->tab_words, b->rk4, b->cone, b->reg, s);
   hipGraph_t g = nullptr;
   hipError_t ce = hipStreamEndCapture(s, &g);
   if (le != hipSuccess || ce != hipSuccess) {
@@ -1189,7 +1207,7 @@ mjh_status mjh_autotune(mjh_batch* b, int32_t nstep_probe, const char* cache_pat
     for (int rep = 0; good && rep < 2; rep++) {  // the first run warms caches
       good = restore() && hip_ok(hipEventRecord(e0, nullptr), "autotune: event") &&
              hip_ok(launch_step(b->d_groups, b->d_tasks, b->ntask, nstep_probe, b->block,
-                                b->lds_bytes, b->tab_words, b->rk4, b->cone, nullptr),
+                                b->lds_bytes, b->tab_words, b->rk4, b->cone, b->reg, nullptr),
                     "autotune: probe launch") &&
              hip_ok(hipEventRecord(e1, nullptr), "autotune: event") &&
              hip_ok(hipEventSynchronize(e1), "autotune: probe") &&

@@ -34,6 +34,10 @@ DEV int opaque_zero() {
 }
 
 
+}  // namespace mjh
+#include "mjh_lanes.h"
+namespace mjh {
+
 // ------------------------------------------------------------------- team helpers
 struct Team {
   int lane;       // 0 .. T-1
@@ -2641,6 +2645,10 @@ DEV void integrate(const DevModel& m, float* W, const Team& t, int& status) {
   t.sync();
 }
 
+}  // namespace mjh
+#include "mjh_newton_reg.h"
+namespace mjh {
+
 // ------------------------------------------------------------- one full step
 // Phase timing for profiling builds only (-DMJH_PHASE_TIMING): every lane accumulates
 // cycle counts per phase; release builds compile the marks away.
@@ -2706,13 +2714,15 @@ DEV void implicit_damping(const DevModel& m, float* W, const Team& t) {
   }
 }
 
-template <bool CONE = false>
+// TT, NB: the team size and padded row length of the register-resident solves (NB = 0: the
+// solves in LDS, any team size and model)
+template <bool CONE = false, int TT = 0, int NB = 0>
 DEV void world_step(const DevModel& m, float* W0, const Team& t0, const float* ctrl,
                     int& status, int iters, float gtol = 0.f, long long* ph = nullptr,
                     long long* last = nullptr, const float* dr = nullptr) {
 #define MJH_PHASE_CTX                                   \
   float* W = W0 + opaque_zero();                        \
-  const Team t{t0.lane + opaque_zero(), t0.T, t0.tp};
+  const Team t{t0.lane + opaque_zero(), TT ? TT : t0.T, t0.tp};
   {
     MJH_PHASE_CTX
     actuation(m, W, t, ctrl, dr);
@@ -2732,7 +2742,12 @@ DEV void world_step(const DevModel& m, float* W0, const Team& t0, const float* c
     MJH_PHASE_CTX
     float* a0 = W + m.o_a0;
     const float* frc = W + m.o_frc;
-    if (m.nv <= t.T) {
+    if constexpr (NB > 0) {
+      const int i = TT == 64 ? t.lane & 31 : t.lane;
+      const float x = smooth_solve_reg<TT, NB>(m, W, t, i < m.nv ? frc[i] : 0.f, false);
+      if (i < m.nv) a0[i] = x;
+      t.sync();
+    } else if (m.nv <= t.T) {
       // a0 = M^-1 frc by the blocked dense Cholesky of the Newton Hessian with no rows:
       // two barriers per four columns take fewer dependent steps than the tree LTDL's
       // one barrier per dof.  It factors M in reversed dof order (leaves first, the
@@ -2769,12 +2784,18 @@ DEV void world_step(const DevModel& m, float* W0, const Team& t0, const float* c
   }
   {
     MJH_PHASE_CTX
-    newton<CONE>(m, W, t, status, iters, gtol);
+    if constexpr (NB > 0) {
+      if (has_bounds(m)) newton_reg<TT, NB, true>(m, W, t, status, iters, gtol);
+      else newton_reg<TT, NB, false>(m, W, t, status, iters, gtol);
+    } else {
+      newton<CONE>(m, W, t, status, iters, gtol);
+    }
     MJH_MARK(6);
   }
   if (m.implicit) {
     MJH_PHASE_CTX
-    implicit_damping(m, W, t);
+    if constexpr (NB > 0) implicit_damping_reg<TT, NB>(m, W, t);
+    else implicit_damping(m, W, t);
   }
 #undef MJH_PHASE_CTX
 }

@@ -13,12 +13,43 @@ __host__ __device__ inline int table_words(const DevModel& m) {
   return ((m.ntri + 3) / 4 + 3) & ~3;
 }
 
+// Launch shape of the register-resident solves: team size and padded row length (0: the
+// batch takes the solves in LDS; team 0: a batch whose groups have different shapes).
+struct RegShape {
+  int team = 0, nb = 0;
+};
+// The shape for worlds of this model on `team` lanes; nb = 0 where the solves stay in LDS: a
+// world that does not fit its team (16 lanes, more than 16 dofs) or has more than 28 dofs (two
+// matrix rows a lane would not leave the registers of two waves per SIMD), contacts other than
+// condim-3 pyramids (the quad-per-contact layout), and at most 16 dofs on 64 lanes (never a
+// default shape).  Where both run, the registers are 1.9 to 2.6 times faster (mjh_newton_reg.h).
+inline RegShape reg_shape(const DevModel& m, int team) {
+  RegShape r;
+  if (!m.jframe || m.cone || m.nv < 1 || m.nv > 28) return r;
+  const int nb = m.nv <= 16 ? 16 : m.nv <= 20 ? 20 : 28;
+  if (team == 16 ? nb != 16 : team == 64 ? nb == 16 : team != 32) return r;
+  r.team = team;
+  r.nb = nb;
+  return r;
+}
+// Whether a batch of several shapes has a register-resident kernel for this one.
+inline bool mix_shape(const RegShape& r) {
+  return (r.team == 16 && r.nb == 16) || (r.team == 32 && r.nb == 20) ||
+         (r.team == 64 && r.nb == 28);
+}
+// Whether the env step has a register-resident kernel for this shape.
+inline bool env_reg_shape(const RegShape& r, bool rk4) { return r.team == 32 && r.nb == 20 && !rk4; }
+
 // Launch the step kernel: one work-group of `block` threads per task; rk4 selects the
 // instantiation that can run fourth-order Runge-Kutta groups, cone the one that can
 // also solve elliptic-cone models.
 hipError_t launch_step(const DevGroup* groups, const DevTask* tasks, int ntask, int nstep,
                        int block, size_t lds_bytes, int tab_words, bool rk4, bool cone,
-                       hipStream_t stream);
+                       RegShape reg, hipStream_t stream);
+hipError_t launch_step_reg(const DevGroup* groups, const DevTask* tasks, int ntask, int nstep,
+                           int block, size_t lds_bytes, bool rk4, RegShape reg,
+                           hipStream_t stream);
+hipError_t set_reg_lds_limit(size_t bytes);
 // Allow the step kernel `bytes` of dynamic LDS per work-group.
 hipError_t set_step_lds_limit(size_t bytes);
 // Compute body_invweight of a freshly uploaded model (one work-group).
@@ -42,7 +73,10 @@ struct EnvArgs {
 // ap_words: LDS words after the pair table for the teams' previous actions
 hipError_t launch_env(const DevGroup* groups, const DevTask* tasks, int ntask, const EnvArgs& E,
                       int block, size_t lds_bytes, int tab_words, int ap_words, bool rk4,
-                      hipStream_t stream);
+                      RegShape reg, hipStream_t stream);
+hipError_t launch_env_reg(const DevGroup* groups, const DevTask* tasks, int ntask,
+                          const EnvArgs& E, int block, size_t lds_bytes, int tab_words,
+                          int ap_words, hipStream_t stream);
 hipError_t set_env_lds_limit(size_t bytes);
 
 }  // namespace mjh

@@ -1,0 +1,578 @@
+// The smooth solve, the Newton solve and the implicit velocity update with one dof per lane
+// and the matrices' rows in registers (mjh_lanes.h), for worlds of at most 28 dofs that fit
+// their team and whose contacts are all condim-3 pyramids (DevModel::jframe).  The
+// mathematics is newton_impl's; what differs is where things live:
+//   - row i of M, then of the Newton Hessian H and of its inverse, are in lane i's registers;
+//   - a contact's four edge rows are on the four lanes of a quad (lane r of a chunk of T rows
+//     holds edge r), so that the edges J_n +- mu J_tk of a product come from the frame rows'
+//     products by quad permutations;
+//   - H's contact part is a matrix-core contraction over the frame rows (32-lane teams: two
+//     worlds at once, one 32 x 32 block each);
+//   - limit and friction-loss rows are unit vectors: they add to one dof's gradient and to
+//     one diagonal entry;
+//   - control flow is uniform in the wavefront and every lane is active: a team that is done
+//     runs along without updating, because matrix instructions and lane swaps take all lanes.
+// The solves in LDS were bound by their serial chains: every entry of a triangular solve and
+// every four columns of a factor waited for an LDS or readlane round trip, and packed indices
+// were unranked per entry.  Measured against them: 8192 quadrupeds x 3 steps 662 -> 323 us,
+// 64 x 4 steps 530 -> 204 us, 2048 humanoids x 2 steps 491 -> 200 us, 8192 hands x 4 steps
+// 2079 -> 1120 us.
+#pragma once
+
+namespace mjh {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// the largest of the wavefront's teams' values, as a scalar
+template <int T>
+DEV int wave_max(int v) {
+  int r = __builtin_amdgcn_readlane(v, 0);
+  if constexpr (T <= 32) r = max(r, __builtin_amdgcn_readlane(v, 32));
+  if constexpr (T == 16)
+    r = max(r, max(__builtin_amdgcn_readlane(v, 16), __builtin_amdgcn_readlane(v, 48)));
+  return r;
+}
+// whether some lane of this team has the flag set
+template <int T>
+DEV bool team_any(bool f, int lane) {
+  const unsigned long long b = __ballot(f);
+  if constexpr (T == 64) return b != 0;
+  const int base = (int)(threadIdx.x & 63) - lane;
+  return ((b >> base) & ((1ull << (T & 63)) - 1ull)) != 0;
+}
+// sum over the dofs (a 64-lane team holds each twice)
+template <int T>
+DEV float dof_sum(const Team& t, float v) {
+  return Team{t.lane, T == 16 ? 16 : 32, t.tp}.sum(v);
+}
+template <int T>
+DEV float dof_max(const Team& t, float v) {
+  return Team{t.lane, T == 16 ? 16 : 32, t.tp}.max(v);
+}
+
+// row i of a packed symmetric matrix (zeros for lanes past nv and past nv in the row)
+template <int NB>
+DEV void load_row(const float* M, int i, int nv, float* A) {
+#pragma unroll
+  for (int j = 0; j < NB; j++) A[j] = 0.f;
+  if (i < nv) {
+    int at = tri(i, 0);
+#pragma unroll
+    for (int j = 0; j < NB; j++) {
+      if (j < min_nv<NB>() || j < nv) A[j] = M[at];
+      at += j < i ? 1 : j + 1;
+    }
+  }
+}
+
+// x_i = (A^-1 rhs)_i for the mass matrix in o_M, plus h diag(dof_vgain) with hgain
+template <int T, int NB>
+DEV float smooth_solve_reg(const DevModel& m, float* W, const Team& t, float rhs, bool hgain) {
+  const int i = T == 64 ? t.lane & 31 : t.lane, nv = m.nv;
+  float A[NB];
+  load_row<NB>(W + m.o_M, i, nv, A);
+  if (hgain) {
+    const float h = i < nv ? m.dt * m.dof_vgain[i] : 0.f;
+#pragma unroll
+    for (int j = 0; j < NB; j++) A[j] += j == i ? h : 0.f;
+  }
+  bool ok = true;
+  return gj_solve<T, NB>(A, nv, i, rhs, ok);
+}
+
+// The constraint rows as the solvers see them.
+template <int T, int NB>
+struct RegRows {
+  const DevModel& m;
+  float* const W0;
+  const int lane0;
+  float* W;
+  Team t;
+  int i, nv, nrow, ncon, no, nl;  // dof of this lane; rows, contacts, others, active limits
+  int ncu, nou;                   // the wavefront's largest contact and other-row counts
+  bool dv;
+
+  // a context of its own for the phase that follows (see opaque_zero)
+  DEV void phase() {
+    W = W0 + opaque_zero();
+    t.lane = lane0 + opaque_zero();
+  }
+  DEV RegRows(const DevModel& m_, float* W_, const Team& t_)
+      : m(m_), W0(W_), lane0(t_.lane), W(W_), t(t_) {
+    const int* scal = (const int*)(W + m.o_scal);
+    i = T == 64 ? t.lane & 31 : t.lane;
+    nv = m.nv;
+    dv = i < nv;
+    nrow = scal[SC_NROW];
+    ncon = scal[SC_NCON];
+    no = nrow - 4 * ncon;
+    nl = no - m.nfric - m.neqrow;
+    ncu = wave_max<T>(ncon);
+    nou = wave_max<T>(no);
+  }
+  // J row f . x (all lanes take part; finite rows only)
+  DEV float j_dot(int f, const Pair& x) const {
+    const float* Jr = W + m.o_J + f * nv;
+    float J[NB];
+#pragma unroll
+    for (int j = 0; j < NB; j++) {
+      J[j] = 0.f;
+      if (j < min_nv<NB>() || j < nv) J[j] = Jr[j];
+    }
+    return row_dot<NB>(J, x);
+  }
+  DEV float mu(int c) const { return W[m.o_con + kConRec * c + 13]; }
+  // f(r, v) for every row r of the world that this lane holds, v = J_r x (x: this lane's
+  // entry of a dof vector).  A contact's quad: lanes 0, 1, 2 form J_n x, J_t1 x, J_t2 x.
+  template <class F>
+  DEV void times(float x, F f) const {
+    const Pair xr = rep_dof<T>(x);
+    const int q = t.lane & 3;
+    for (int cb = 0; cb < ncu; cb += T / 4) {
+      const int c = cb + (t.lane >> 2);
+      const bool act = c < ncon;
+      const float v = j_dot(act ? 3 * c + min(q, 2) : 0, xr);
+      const float vn = quad_perm<0x00>(v), vt = quad_perm<0xA5>(v);
+      const float mc = act ? mu(c) : 0.f;
+      if (act) f(4 * c + q, vn + ((q & 1) ? -mc : mc) * vt);
+    }
+    for (int kb = 0; kb < nou; kb += T) {
+      const int k = kb + t.lane;
+      const bool act = k < no;
+      int dof = 0;
+      float sg = 1.f;
+      bool unit = true;
+      if (act && k < nl) limit_sign(k, dof, sg);
+      else if (act && k < nl + m.nfric) dof = m.fric_dadr[k - nl];
+      else unit = !act;
+      float v = sg * from_dof(x, dof);
+      if (m.neqrow > 0) {
+        const float vd = j_dot(act ? 3 * ncon + k : 0, xr);
+        v = unit ? v : vd;
+      }
+      if (act) f(4 * ncon + k, v);
+    }
+  }
+  DEV float from_dof(float x, int dof) const {
+    const int base = (int)(threadIdx.x & 63) - t.lane;
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (base + dof), __float_as_int(x)));
+  }
+  DEV void limit_sign(int k, int& dof, float& sg) const {
+    const int code = ((const int*)(W + m.o_lim))[k];
+    dof = m.lim_dadr[code & 0xffff];
+    sg = (code >> 16) ? -1.f : 1.f;
+  }
+  // the words of Newton's vectors in LDS are free here: per-dof slots of the unit rows
+  DEV float* unit_slots(int which) const { return W + m.o_Mr + which * nv; }
+  DEV void clear_units() const {
+    if (nou > 0)
+      for (int k = t.lane; k < 4 * nv; k += T) unit_slots(0)[k] = 0.f;
+  }
+  // scatter y(r) (times the row's sign when signed) of the unit rows into two slots per dof:
+  // a dof has at most one active limit and one friction-loss row
+  template <class Y>
+  DEV void put_units(int slot, bool sign, Y y) const {
+    for (int kb = 0; kb < nou; kb += T) {
+      const int k = kb + t.lane;
+      if (k < nl) {
+        int dof;
+        float sg;
+        limit_sign(k, dof, sg);
+        unit_slots(slot)[dof] = sign ? sg * y(4 * ncon + k) : y(4 * ncon + k);
+      } else if (k < nl + m.nfric) {
+        unit_slots(slot + 1)[m.fric_dadr[k - nl]] = y(4 * ncon + k);
+      }
+    }
+  }
+  DEV float get_units(int slot) const {
+    return dv && nou > 0 ? unit_slots(slot)[i] + unit_slots(slot + 1)[i] : 0.f;
+  }
+  // entry i of frame rows 3c, 3c + 1, 3c + 2 (0 past this world's contacts and dofs)
+  DEV void frame_col(int c, float& n, float& a, float& b) const {
+    const float* Jc = W + m.o_J + 3 * c * nv + i;
+    n = a = b = 0.f;
+    if (dv && c < ncon) {
+      n = Jc[0];
+      a = Jc[nv];
+      b = Jc[2 * nv];
+    }
+  }
+  // init_i + sum_r y(r) J_ri, y a functor over this world's rows
+  template <class Y>
+  DEV float t_times(Y y, float init) const {
+    float* fy = W + m.o_fw;
+    const int q = t.lane & 3;
+    for (int cb = 0; cb < ncu; cb += T / 4) {
+      const int c = cb + (t.lane >> 2);
+      const bool act = c < ncon;
+      const float yr = act ? y(4 * c + q) : 0.f, mc = act ? mu(c) : 0.f;
+      const float yx = quad_perm<kXor1>(yr);
+      const float sm = yr + yx, df = yr - yx;  // lanes 0 and 2: the pairs' sums, differences
+      const float all = sm + quad_perm<kXor2>(sm);
+      if (c < ncu && !(q & 1)) {
+        if (q == 0) fy[3 * c] = all;
+        fy[3 * c + 1 + (q >> 1)] = mc * df;
+      }
+    }
+    put_units(0, true, y);
+    t.sync();
+    float v = init;
+    for (int c = 0; c < ncu; c++) {
+      float n, a, b;
+      frame_col(c, n, a, b);
+      v += fy[3 * c] * n;
+      v += fy[3 * c + 1] * a;
+      v += fy[3 * c + 2] * b;
+    }
+    v += get_units(0);
+    const int e0 = 3 * ncon + nl + m.nfric;  // the equality rows, always present
+    for (int k = 0; k < m.neqrow; k++)
+      if (dv && nrow > 0) v += y(4 * ncon + nl + m.nfric + k) * W[m.o_J + (e0 + k) * nv + i];
+    t.sync();
+    return v;
+  }
+  // A = Mrow + sum_r w(r) J_ri J_r. (row i of the Hessian), w the rows' weights
+  template <class Wt>
+  DEV void hessian(const float* Mrow, Wt w, float* A) const {
+    float* cf = W + m.o_fw;
+    const int q = t.lane & 3;
+    for (int cb = 0; cb < ncu; cb += T / 4) {
+      const int c = cb + (t.lane >> 2);
+      const bool act = c < ncon;
+      const float wr = act ? w(4 * c + q) : 0.f, mc = act ? mu(c) : 0.f;
+      const float wx = quad_perm<kXor1>(wr);
+      const float sm = wr + wx, df = wr - wx;
+      const float all = sm + quad_perm<kXor2>(sm);
+      if (c < ncu && !(q & 1)) {
+        if (q == 0) cf[5 * c] = all;
+        cf[5 * c + 1 + q] = mc * df;
+        cf[5 * c + 2 + q] = mc * mc * sm;
+      }
+    }
+    put_units(2, false, w);
+    t.sync();
+    // a contact adds P J3 over its frames, P = J3^T C: rows P_f of this lane's dof
+    const int e0 = 3 * ncon + nl + m.nfric;
+    if constexpr (T == 64) {
+      f32x16 C;
+#pragma unroll
+      for (int v = 0; v < 16; v++) C[v] = 0.f;
+      const bool up = t.lane >= 32;
+      for (int c = 0; c < ncu; c++) {
+        float n, a, b;
+        frame_col(c, n, a, b);
+        const float* k = cf + 5 * c;
+        const float pn = k[0] * n + k[1] * a + k[3] * b;
+        const float pa = k[1] * n + k[2] * a, pb = k[3] * n + k[4] * b;
+        C = __builtin_amdgcn_mfma_f32_32x32x2f32(up ? pa : pn, up ? a : n, C, 0, 0, 0);
+        C = __builtin_amdgcn_mfma_f32_32x32x2f32(up ? 0.f : pb, up ? 0.f : b, C, 0, 0, 0);
+      }
+      for (int k = 0; k < m.neqrow; k++) {
+        const float j = dv && nrow > 0 ? W[m.o_J + (e0 + k) * nv + i] : 0.f;
+        const float wk = nrow > 0 ? w(4 * ncon + nl + m.nfric + k) : 0.f;
+        C = __builtin_amdgcn_mfma_f32_32x32x2f32(up ? 0.f : wk * j, up ? 0.f : j, C, 0, 0, 0);
+      }
+      // accumulator register v of lane l: entry (8 (v / 4) + 4 (l / 32) + v % 4, l % 32)
+#pragma unroll
+      for (int v = 0; v < 16; v++) {
+        const Pair h = swap32(C[v], C[v]);
+        const int r = 8 * (v >> 2) + (v & 3);
+        if (r < NB) A[r] = h.a + Mrow[r];
+        if (r + 4 < NB) A[r + 4] = h.b + Mrow[r + 4];
+      }
+    } else if constexpr (T == 32) {
+      f32x32 C;  // block 0: the wavefront's first world, block 1 its second
+#pragma unroll
+      for (int v = 0; v < 32; v++) C[v] = 0.f;
+      for (int c = 0; c < ncu; c++) {
+        float n, a, b;
+        frame_col(c, n, a, b);
+        const float* k = cf + 5 * c;
+        const float pn = k[0] * n + k[1] * a + k[3] * b;
+        const float pa = k[1] * n + k[2] * a, pb = k[3] * n + k[4] * b;
+        C = __builtin_amdgcn_mfma_f32_32x32x1f32(pn, n, C, 0, 0, 0);
+        C = __builtin_amdgcn_mfma_f32_32x32x1f32(pa, a, C, 0, 0, 0);
+        C = __builtin_amdgcn_mfma_f32_32x32x1f32(pb, b, C, 0, 0, 0);
+      }
+      for (int k = 0; k < m.neqrow; k++) {
+        const float j = dv && nrow > 0 ? W[m.o_J + (e0 + k) * nv + i] : 0.f;
+        const float wk = nrow > 0 ? w(4 * ncon + nl + m.nfric + k) : 0.f;
+        C = __builtin_amdgcn_mfma_f32_32x32x1f32(wk * j, j, C, 0, 0, 0);
+      }
+      // block B's register v of lane l: its entry (8 (v / 4) + 4 (l / 32) + v % 4, l % 32);
+      // the swap gives each half-wavefront its own block's two row groups
+#pragma unroll
+      for (int v = 0; v < 16; v++) {
+        const Pair h = swap32(C[v], C[16 + v]);
+        const int r = 8 * (v >> 2) + (v & 3);
+        if (r < NB) A[r] = h.a + Mrow[r];
+        if (r + 4 < NB) A[r + 4] = h.b + Mrow[r + 4];
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < NB; j++) A[j] = Mrow[j];
+      for (int c = 0; c < ncu; c++) {
+        float n, a, b;
+        frame_col(c, n, a, b);
+        const float* k = cf + 5 * c;
+        const float pn = k[0] * n + k[1] * a + k[3] * b;
+        const float pa = k[1] * n + k[2] * a, pb = k[3] * n + k[4] * b;
+        dpp_axpy<16>(A, n, pn);
+        dpp_axpy<16>(A, a, pa);
+        dpp_axpy<16>(A, b, pb);
+      }
+      for (int k = 0; k < m.neqrow; k++) {
+        const float j = dv && nrow > 0 ? W[m.o_J + (e0 + k) * nv + i] : 0.f;
+        const float wk = nrow > 0 ? w(4 * ncon + nl + m.nfric + k) : 0.f;
+        dpp_axpy<16>(A, j, wk * j);
+      }
+    }
+    if (nou > 0) {
+      const float du = get_units(2);
+#pragma unroll
+      for (int j = 0; j < NB; j++) A[j] += j == i ? du : 0.f;
+    }
+    t.sync();
+  }
+};
+
+// sum over the 16 rows held by one replicated 16-lane row (up to n of them, n uniform) of the
+// line search's slope terms
+template <int B = 0>
+DEV float slope_rows(float dp, float e, float s, float ds, float br, int n) {
+  if (n > B) {
+    dp = dpp_slope4<B>(dp, e, s, ds, br);
+    if constexpr (B < 12) return slope_rows<B + 4>(dp, e, s, ds, br, n);
+  }
+  return dp;
+}
+// the same for rows with a force bound F (row_slope): one row per step
+template <int K = 0>
+DEV float slope_rows_fr(float dp, float e, float s, float D, float F, float br, int n) {
+  if (n > K) {
+    const float sq = row_bcast<K>(s);
+    dp += sq * row_slope(row_bcast<K>(D), row_bcast<K>(F), row_bcast<K>(e) + br * sq);
+    if constexpr (K < 15) return slope_rows_fr<K + 1>(dp, e, s, D, F, br, n);
+  }
+  return dp;
+}
+// a row vector's 16-lane rows, each replicated over the team
+template <int T>
+struct RowRep {
+  float r[T / 16];
+  DEV explicit RowRep(float x) {
+    if constexpr (T == 16) {
+      r[0] = x;
+    } else if constexpr (T == 32) {
+      const Pair p = swap16(x);
+      r[0] = p.a;
+      r[1] = p.b;
+    } else {
+      const Pair h = swap32(x, x), lo = swap16(h.a), hi = swap16(h.b);
+      r[0] = lo.a;
+      r[1] = lo.b;
+      r[2] = hi.a;
+      r[3] = hi.b;
+    }
+  }
+};
+
+// newton_impl's solve (see there for the steps and the stopping rules)
+template <int T, int NB, bool FR>
+DEV void newton_reg(const DevModel& m, float* W0, const Team& t0, int& status, int iters,
+                    float gtol) {
+  RegRows<T, NB> R(m, W0, t0);
+  const Team& t = R.t;
+  // the row arrays (through the phase's base, so that no address is held across phases)
+  auto e = [&](int r) -> float& { return R.W[m.o_e + r]; };   // J a - aref
+  auto s = [&](int r) -> float& { return R.W[m.o_s + r]; };   // J delta
+  auto D = [&](int r) { return R.W[m.o_D + r]; };
+  auto fl = [&](int r) { return FR ? R.W[m.o_fl + r] : 0.f; };
+  const int nrow = R.nrow, i = R.i, nv = m.nv;
+  const bool dv = R.dv;
+  const int nru = wave_max<T>(nrow);
+  const float a0 = dv ? R.W[m.o_a0 + i] : 0.f;
+  if (nru == 0) {
+    if (dv) R.W[m.o_qacc + i] = a0;
+    t.sync();
+    return;
+  }
+  bool done = nrow == 0;
+  float a = dv ? R.W[m.o_qacc + i] : 0.f;
+  float Mrow[NB];
+  load_row<NB>(R.W + m.o_M, i, nv, Mrow);
+  R.clear_units();  // (the poses and motion subspaces there are dead from here on)
+  // ---- start point: cost of the warm start vs cost of a0
+  float Mr = row_dot<NB>(Mrow, rep_dof<T>(a - a0));
+  float cw = 0.f, c0 = 0.f;
+  auto cost = [&](int r, float v) {
+    return FR ? row_cost(D(r), fl(r), v) : (v < 0.f ? 0.5f * D(r) * v * v : 0.f);
+  };
+  R.times(a, [&](int r, float v) {
+    v -= R.W[m.o_aref + r];
+    cw += cost(r, v);
+    e(r) = v;
+  });
+  R.times(a0, [&](int r, float v) {
+    v -= R.W[m.o_aref + r];
+    c0 += cost(r, v);
+    s(r) = v;
+  });
+  cw = t.sum(cw) + dof_sum<T>(t, 0.5f * (a - a0) * Mr);
+  c0 = t.sum(c0);
+  t.sync();
+  if (!(cw <= c0) || done) {
+    a = a0;
+    Mr = 0.f;
+    for (int r = t.lane; r < nrow; r += T) e(r) = s(r);
+  }
+  t.sync();
+  float gstop = 0.f;
+  if (gtol > 0.f) gstop = gtol * dof_max<T>(t, fmaxf(1.f, dv ? fabsf(R.W[m.o_frc + i]) : 0.f));
+  auto quad = [&](int r) { return FR ? row_quad(D(r), fl(r), e(r)) : e(r) < 0.f; };
+  auto rep = [&](float x) { return rep_dof<T>(x); };
+  float A[NB], sc = 1.f;  // the Hessian's inverse: row -sc A
+#pragma unroll
+  for (int j = 0; j < NB; j++) A[j] = 0.f;
+  bool kept = false;      // A holds the inverse at the current pieces
+  for (int it = 0; it < iters; it++) {
+    R.phase();
+    const float g = R.t_times([&](int r) {
+      const float er = e(r);
+      return FR ? row_slope(D(r), fl(r), er) : (er < 0.f ? D(r) * er : 0.f);
+    }, Mr);
+    if (gtol > 0.f) done = done || dof_max<T>(t, fabsf(g)) <= gstop;
+    if (!__ballot(!done)) break;
+    // ---- delta = -H^-1 g.  With no piece changed by the last step the inverse is that of the
+    // last iteration (and comes out the same if the wavefront's other world needs a new one);
+    // then the direction is a product with it, else it comes out of the elimination.
+    float de = 0.f;
+    bool ok = true;
+    if (__ballot(!done && !kept)) {
+      R.phase();
+      R.hessian(Mrow, [&](int r) { return quad(r) ? D(r) : 0.f; }, A);
+      de = sweep_inverse<T, NB>(A, sc, nv, i, -g, ok);
+    }
+    float d = sc * row_dot<NB>(A, rep(g));
+    if (!kept) {
+      d = de;
+      if (!done && !ok) {
+        status |= 4;
+        done = true;
+      }
+    }
+    // ---- one step of iterative refinement, H applied unassembled
+    R.phase();
+    R.times(d, [&](int r, float v) { s(r) = quad(r) ? D(r) * v : 0.f; });
+    const float res = R.t_times([&](int r) { return s(r); }, row_dot<NB>(Mrow, rep(d), g));
+    const float corr = -sc * row_dot<NB>(A, rep(res));
+    d -= corr;
+    const float cm = dof_max<T>(t, fabsf(corr));
+    // ---- line search quantities
+    R.phase();
+    const float Md = row_dot<NB>(Mrow, rep(d));
+    R.times(d, [&](int r, float v) { s(r) = v; });
+    const float gd = dof_sum<T>(t, g * d), dMd = dof_sum<T>(t, d * Md),
+                dMr = dof_sum<T>(t, d * Mr);
+    t.sync();
+    done = done || !(gd < 0.f);
+    // ---- phi' at every positive breakpoint (one candidate a lane)
+    float lo = 0.f, hi = INFINITY;
+    const int nbp = FR ? nrow + m.nfric : nrow;
+    const int nbu = FR ? nru + m.nfric : nru;
+    const int nfr0 = nrow - m.nfric - m.neqrow;  // first friction-loss row
+    for (int cb = 0; cb < nbu; cb += T) {
+      const int c = cb + t.lane;
+      float br = 0.f;
+      if (c < nbp) {
+        const int r = c < nrow ? c : nfr0 + (c - nrow);
+        const float sr = s(r);
+        float at = 0.f;
+        bool use = sr != 0.f;
+        if (FR && fl(r) > 0.f) {
+          use = use && fl(r) != INFINITY;
+          at = (c < nrow ? fl(r) : -fl(r)) / D(r);
+        }
+        if (use) br = (at - e(r)) / sr;
+      }
+      float dp = dMr + br * dMd;
+      for (int rb = 0; rb < nru; rb += T) {
+        const int r = rb + t.lane;
+        const bool in = r < nrow;
+        const float er = in ? e(r) : 0.f, sr = in ? s(r) : 0.f, Dr = in ? D(r) : 0.f;
+        const RowRep<T> re(er), rs(sr), rd(FR ? Dr : Dr * sr);
+        const RowRep<T> rf(FR && in ? fl(r) : 0.f);
+#pragma unroll
+        for (int h = 0; h < T / 16; h++) {
+          const int n = nru - rb - 16 * h;
+          if constexpr (FR) dp = slope_rows_fr<>(dp, re.r[h], rs.r[h], rd.r[h], rf.r[h], br, n);
+          else dp = slope_rows<>(dp, re.r[h], rs.r[h], rd.r[h], br, n);
+        }
+      }
+      if (br > 0.f) {
+        if (dp <= 0.f) lo = fmaxf(lo, br);
+        else hi = fminf(hi, br);
+      }
+    }
+    lo = t.max(lo);
+    hi = t.min(hi);
+    R.phase();
+    const float probe = (hi < INFINITY) ? 0.5f * (lo + hi) : lo + 1.f;
+    float Ac = 0.f, Bc = 0.f;
+    for (int r = t.lane; r < nrow; r += T) {
+      const float sr = s(r), er = e(r), Dr = D(r), ep = er + probe * sr;
+      if (FR ? row_quad(Dr, fl(r), ep) : ep < 0.f) {
+        Ac += Dr * sr * er;
+        Bc += Dr * sr * sr;
+      } else if (FR) {
+        Ac += sr * row_slope(Dr, fl(r), ep);
+      }
+    }
+    Ac = t.sum(Ac) + dMr;
+    Bc = t.sum(Bc) + dMd;
+    float al = -Ac / Bc;
+    al = fminf(fmaxf(al, lo), hi);
+    // ---- update
+    bool moved = false;
+    if (!done) {
+      a += al * d;
+      Mr += al * Md;
+      for (int r = t.lane; r < nrow; r += T) {
+        const float e0 = e(r), e1 = e0 + al * s(r);
+        moved = moved || (FR ? (row_piece(D(r), fl(r), e0) != row_piece(D(r), fl(r), e1))
+                             : ((e0 < 0.f) != (e1 < 0.f)));
+        e(r) = e1;
+      }
+    }
+    moved = team_any<T>(moved, R.lane0);
+    const float am = dof_max<T>(t, fmaxf(1.f, fabsf(a)));
+    t.sync();
+    done = done || (!moved && cm <= kNewtonExitTol * am);
+    kept = !moved;
+  }
+  if (dv) R.W[m.o_qacc + i] = a;
+  t.sync();
+}
+
+// implicit_damping with the registers' elimination
+template <int T, int NB>
+DEV void implicit_damping_reg(const DevModel& m, float* W, const Team& t) {
+  const RegRows<T, NB> R(m, W, t);
+  const float* D = W + m.o_D;
+  const float* e = W + m.o_e;
+  const float* fl = W + m.o_fl;
+  const bool fr = has_bounds(m), dv = R.dv;
+  const int i = R.i;
+  float rhs = dv ? W[m.o_frc + i] : 0.f;
+  if (m.implicit == 2 && dv) rhs -= m.dof_hkp[i] * W[m.o_qvel + i];
+  R.clear_units();
+  t.sync();
+  rhs = R.t_times([&](int r) {
+    return -(fr ? row_slope(D[r], fl[r], e[r]) : fminf(D[r] * e[r], 0.f));
+  }, rhs);
+  const float x = smooth_solve_reg<T, NB>(m, W, t, rhs, true);
+  if (dv) W[m.o_frc + i] = x;
+  t.sync();
+}
+
+}  // namespace mjh

@@ -1,0 +1,90 @@
+"""The register-resident solves (one dof per lane, matrix rows in registers) at the edges of
+their row lengths and team sizes, against the FP64 reference.
+
+Rows are padded to 16, 20 or 28 entries; 29 dofs and 17 dofs on 16 lanes take the solves in
+LDS.  Hinge chains cover every edge of the elimination of M (their inertias spread over the
+chain make it ill conditioned, so the gate scales with the condition number: FP32 elimination
+of an SPD matrix is backward stable, error <= c n eps cond).  Contact worlds cover wavefronts
+with one, two and four worlds whose contact counts differ, down to none.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2502_08844_amd.synth import inputs, robots
+from tests.gpu_util import gpu_ctx, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+EPS32 = 2.0 ** -24
+
+
+@pytest.fixture(scope="module")
+def lib():
+    return gpu_ctx()
+
+
+@pytest.mark.parametrize("team", [16, 32, 64])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 20, 21, 28, 29])
+def test_chain_lengths(lib, n, team):
+    mjh, ctx = lib
+    m = robots.hinge_chain(n, damping=0.05)
+    nw = 5
+    r = inputs.rng(n, 11)
+    qp = inputs.f32(r.uniform(-0.6, 0.6, (nw, m.nq)))
+    qv = inputs.f32(r.normal(0.0, 0.5, (nw, m.nv)))
+    o = oracle.Oracle(m)
+    ref = o.step(qp.copy(), qv.copy(), None, None, nstep=1)
+    print(f"[gpu] chain of {n} on {team} lanes", flush=True)
+    g = run_gpu(ctx, mjh, m, qp, qv, None, None, 1, team=team, block=64, contacts=False)
+    for w in range(nw):
+        cond = np.linalg.cond(o.forward(qp[w], qv[w], np.zeros(m.nv), None)["M"])
+        err = np.abs(g["qacc"][w] - ref["qacc"][w]).max() / max(np.abs(ref["qacc"][w]).max(), 9.81)
+        assert err <= 8 * max(n, 4) * EPS32 * max(cond, 10.0), (w, err, cond)
+
+
+@pytest.mark.parametrize("team,block", [(16, 64), (32, 64), (32, 128), (64, 64)])
+@pytest.mark.parametrize("nw", [1, 3, 8])
+def test_wavefront_worlds_with_different_contacts(lib, nw, team, block):
+    """Worlds of one wavefront on the ground, tilted and in the air: each one's accelerations
+    and forces match the reference, and equal those of the world alone bit for bit."""
+    mjh, ctx = lib
+    m = robots.quadruped()
+    qp = np.tile(robots.quadruped_standing_qpos(m), (nw, 1))
+    for w in range(nw):
+        qp[w, 2] += (-0.002, 0.2, 0.001)[w % 3]
+        qp[w, 7:] += inputs.rng(w, 12).uniform(-0.05, 0.05, 12) * (w % 3 > 0)
+    qp = inputs.f32(qp)
+    qv = inputs.f32(inputs.rng(5, 13).normal(0.0, 0.1, (nw, m.nv)))
+    u = inputs.controls("quadruped", m, nw, 1, seed=3)
+    o = oracle.Oracle(m)
+    ref = o.step(qp.copy(), qv.copy(), None, u, nstep=1)
+    print(f"[gpu] {nw} quadrupeds, {team} lanes, work-group {block}", flush=True)
+    g = run_gpu(ctx, mjh, m, qp, qv, None, u, 1, team=team, block=block)
+    assert np.array_equal(g["ncon"], ref["ncon"])
+    err = np.abs(g["qacc"] - ref["qacc"]).max(1) / np.maximum(np.abs(ref["qacc"]).max(1), 9.81)
+    assert err.max() < 1e-4, err
+    weight = m.total_mass() * 9.81
+    df = np.abs(g["contacts"][:, :, 13:16] - ref["contacts"][:, :, 13:16]).max() / weight
+    assert df < 1e-3, df
+    for w in range(nw):
+        one = run_gpu(ctx, mjh, m, qp[w:w + 1], qv[w:w + 1], None, u[:, w:w + 1], 1, team=team,
+                      block=block)
+        assert np.array_equal(one["qacc"][0], g["qacc"][w]), w
+
+
+def test_registers_agree_with_lds_solves(lib):
+    """The same quadruped through the register-resident solves (32 lanes) and the solves in
+    LDS (16 lanes, fewer than its dofs)."""
+    mjh, ctx = lib
+    m = robots.quadruped()
+    nw = 33
+    qp, qv = inputs.initial_state("quadruped", m, nw, seed=21)
+    qp[:, 2] -= 0.004
+    u = inputs.controls("quadruped", m, nw, 1, seed=21)
+    a = run_gpu(ctx, mjh, m, inputs.f32(qp), qv, None, u, 1, team=32, block=128)
+    b = run_gpu(ctx, mjh, m, inputs.f32(qp), qv, None, u, 1, team=16, block=64)
+    err = np.abs(a["qacc"] - b["qacc"]).max(1) / np.maximum(np.abs(b["qacc"]).max(1), 9.81)
+    assert err.max() < 2e-4, err.max()  # both are held to 1e-4 of the reference
+    torch.cuda.synchronize()
