@@ -1,0 +1,12 @@
+#include "mjh_adjoint_dev.h"
+
+namespace mjh {
+
+RolloutKernels rollout_kernels_32_20() {
+  RolloutKernels k;
+  k.fwd = rollout_fwd_kernel<32, 20>;
+  k.bwd = rollout_bwd_kernel<32, 20>;
+  return k;
+}
+
+}  // namespace mjh

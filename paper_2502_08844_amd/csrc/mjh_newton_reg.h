@@ -85,7 +85,7 @@ template <int T, int NB>
 struct RegRows {
   const DevModel& m;
   float* const W0;
-  const int lane0;
+  const int lane0, o_slots;
   float* W;
   Team t;
   int i, nv, nrow, ncon, no, nl;  // dof of this lane; rows, contacts, others, active limits
@@ -97,8 +97,10 @@ struct RegRows {
     W = W0 + opaque_zero();
     t.lane = lane0 + opaque_zero();
   }
-  DEV RegRows(const DevModel& m_, float* W_, const Team& t_)
-      : m(m_), W0(W_), lane0(t_.lane), W(W_), t(t_) {
+  // slots: where the unit rows' per-dof words are, 4 nv (default: Newton's vectors in LDS,
+  // unused by these solves)
+  DEV RegRows(const DevModel& m_, float* W_, const Team& t_, int slots)
+      : m(m_), W0(W_), lane0(t_.lane), o_slots(slots), W(W_), t(t_) {
     const int* scal = (const int*)(W + m.o_scal);
     i = T == 64 ? t.lane & 31 : t.lane;
     nv = m.nv;
@@ -162,8 +164,7 @@ struct RegRows {
     dof = m.lim_dadr[code & 0xffff];
     sg = (code >> 16) ? -1.f : 1.f;
   }
-  // the words of Newton's vectors in LDS are free here: per-dof slots of the unit rows
-  DEV float* unit_slots(int which) const { return W + m.o_Mr + which * nv; }
+  DEV float* unit_slots(int which) const { return W + o_slots + which * nv; }
   DEV void clear_units() const {
     if (nou > 0)
       for (int k = t.lane; k < 4 * nv; k += T) unit_slots(0)[k] = 0.f;
@@ -381,7 +382,7 @@ struct RowRep {
 template <int T, int NB, bool FR>
 DEV void newton_reg(const DevModel& m, float* W0, const Team& t0, int& status, int iters,
                     float gtol) {
-  RegRows<T, NB> R(m, W0, t0);
+  RegRows<T, NB> R(m, W0, t0, m.o_Mr);
   const Team& t = R.t;
   // the row arrays (through the phase's base, so that no address is held across phases)
   auto e = [&](int r) -> float& { return R.W[m.o_e + r]; };   // J a - aref
@@ -557,7 +558,7 @@ DEV void newton_reg(const DevModel& m, float* W0, const Team& t0, int& status, i
 // implicit_damping with the registers' elimination
 template <int T, int NB>
 DEV void implicit_damping_reg(const DevModel& m, float* W, const Team& t) {
-  const RegRows<T, NB> R(m, W, t);
+  const RegRows<T, NB> R(m, W, t, m.o_Mr);
   const float* D = W + m.o_D;
   const float* e = W + m.o_e;
   const float* fl = W + m.o_fl;

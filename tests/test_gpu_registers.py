@@ -88,3 +88,43 @@ def test_registers_agree_with_lds_solves(lib):
     err = np.abs(a["qacc"] - b["qacc"]).max(1) / np.maximum(np.abs(b["qacc"]).max(1), 9.81)
     assert err.max() < 2e-4, err.max()  # both are held to 1e-4 of the reference
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("kind,team", [("quadruped", 32), ("quadruped", 64), ("humanoid", 64)])
+def test_rollout_gradients_of_partial_wavefronts(lib, kind, team):
+    """Three worlds (an odd count: the last wavefront's spare lanes shadow its world) against
+    the same worlds one at a time, bit for bit, and against directional derivatives of the
+    reference (central differences; the gate is the adjoint's, 1e-3 of |grad| |d|)."""
+    mjh, ctx = lib
+    m = robots.WORKLOADS[kind]()
+    H, nw = 6, 3
+    qp, qv = inputs.initial_state(kind, m, nw, seed=8)
+    qp[:, 2] -= 0.003
+    qp = inputs.f32(qp)
+    u = inputs.controls(kind, m, nw, H, seed=8)
+
+    def grads(ws):
+        w = mjh.World(ctx, m, len(ws), qpos=qp[ws])
+        w.batch.set_launch(0, team, 64)
+        v = torch.tensor(qv[ws], dtype=torch.float32, device="cuda", requires_grad=True)
+        c = torch.tensor(u[:, ws], dtype=torch.float32, device="cuda", requires_grad=True)
+        mjh.Rollout.apply(v, c, w, H, 4).sum().backward()
+        return v.grad.cpu().numpy(), c.grad.cpu().numpy()
+
+    print(f"[gpu] rollout gradients, {nw} x {kind} on {team} lanes", flush=True)
+    gv, gc = grads([0, 1, 2])
+    for w in range(nw):
+        v1, c1 = grads([w])
+        assert np.array_equal(v1[0], gv[w]) and np.array_equal(c1[:, 0], gc[:, w]), w
+    o = oracle.Oracle(m)
+    r = inputs.rng(8, 21)
+    for _ in range(3):
+        dv, dc = r.normal(size=gv.shape), r.normal(size=gc.shape)
+        h = 1e-6
+        up = o.rollout_loss(qp, qv + h * dv, u + h * dc, mode=oracle.MODE_CONVERGED)
+        dn = o.rollout_loss(qp, qv - h * dv, u - h * dc, mode=oracle.MODE_CONVERGED)
+        want = (up - dn) / (2 * h)
+        got = (gv * dv).sum(1) + (gc * dc).sum((0, 2))
+        scale = np.sqrt((gv ** 2).sum(1) + (gc ** 2).sum((0, 2))) * np.sqrt(
+            (dv ** 2).sum(1) + (dc ** 2).sum((0, 2)))
+        assert np.all(np.abs(got - want) <= 1e-3 * scale), (got, want, scale)
