@@ -425,6 +425,16 @@ mjh_status compile_model(const HostModel& h, ModelRec& rec, Packer& pk, std::str
     ncand += pair_slots(kind);
   }
   d.ncand = ncand;
+  std::vector<int> pair_order;
+  auto list_pairs = [&](auto want) {
+    const size_t n0 = pair_order.size();
+    for (int p = 0; p < h.npair; p++)
+      if (want(pair_kind[p])) pair_order.push_back(p);
+    return (int)(pair_order.size() - n0);
+  };
+  d.nsimple = list_pairs([](int k) { return k != PK_CAPSULE_BOX && k != PK_SPHERE_HFIELD; });
+  d.ncapbox = list_pairs([](int k) { return k == PK_CAPSULE_BOX; });
+  d.nhfpair = list_pairs([](int k) { return k == PK_SPHERE_HFIELD; });
   d.nlevel = nlevel;
   d.nmpair = (int)mpair.size();
   d.ntri = h.nv * (h.nv + 1) / 2;
@@ -470,6 +480,7 @@ mjh_status compile_model(const HostModel& h, ModelRec& rec, Packer& pk, std::str
   pk.add(h.pair_g2, &d.pair_g2);
   pk.add(pair_kind, &d.pair_kind);
   pk.add(pair_candadr, &d.pair_candadr);
+  pk.add(pair_order, &d.pair_order);
   pk.add(cand_pair, &d.cand_pair);
   pk.add(h.act_type, &d.act_type);
   pk.add(act_qadr, &d.act_qadr);

@@ -50,6 +50,7 @@ struct DevModel {
                  // 3c + 2, its edges rows 4c .. 4c + 3 of the per-row arrays, and a
                  // non-contact row r >= 4 ncon is J row r - ncon.
   int iterations, nlevel, nmpair, ntri;
+  int nsimple, ncapbox, nhfpair;  // pair counts of the three searches of collide_candidates
   int implicit;  // 1: joint damping and PD velocity gains integrated implicitly;
                  // 2: also the PD position gains
   int rk4;       // 1: fourth-order Runge-Kutta (forward pass at four stages)
@@ -86,6 +87,8 @@ struct DevModel {
   const int* pair_g2;
   const int* pair_kind;
   const int* pair_candadr;  // first candidate slot of each pair
+  const int* pair_order;    // pairs by search: nsimple one lane each, then ncapbox capsule-box
+                            // (four lanes each), then nhfpair heightfield (eight lanes each)
   const int* cand_pair;     // [ncand] owning pair
   const int* act_type;
   const int* act_qadr;
