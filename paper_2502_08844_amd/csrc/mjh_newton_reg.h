@@ -112,7 +112,8 @@ struct RegRows {
     ncu = wave_max<T>(ncon);
     nou = wave_max<T>(no);
   }
-  // J row f . x (all lanes take part; finite rows only)
+  // J row f . x (all lanes take part; finite rows only); FINE: summed in FP64
+  template <bool FINE>
   DEV float j_dot(int f, const Pair& x) const {
     const float* Jr = W + m.o_J + f * nv;
     float J[NB];
@@ -121,19 +122,29 @@ struct RegRows {
       J[j] = 0.f;
       if (j < min_nv<NB>() || j < nv) J[j] = Jr[j];
     }
+    if constexpr (FINE) {
+      double acc = 0.0;
+      fine_dot<0>(acc, J, x);
+      return (float)acc;
+    }
     return row_dot<NB>(J, x);
+  }
+  template <int K>
+  DEV void fine_dot(double& acc, const float* J, const Pair& x) const {
+    acc += (double)J[K] * (double)row_bcast<(K & 15)>(K < 16 ? x.a : x.b);
+    if constexpr (K + 1 < NB) fine_dot<K + 1>(acc, J, x);
   }
   DEV float mu(int c) const { return W[m.o_con + kConRec * c + 13]; }
   // f(r, v) for every row r of the world that this lane holds, v = J_r x (x: this lane's
   // entry of a dof vector).  A contact's quad: lanes 0, 1, 2 form J_n x, J_t1 x, J_t2 x.
-  template <class F>
+  template <bool FINE = false, class F>
   DEV void times(float x, F f) const {
     const Pair xr = rep_dof<T>(x);
     const int q = t.lane & 3;
     for (int cb = 0; cb < ncu; cb += T / 4) {
       const int c = cb + (t.lane >> 2);
       const bool act = c < ncon;
-      const float v = j_dot(act ? 3 * c + min(q, 2) : 0, xr);
+      const float v = j_dot<FINE>(act ? 3 * c + min(q, 2) : 0, xr);
       const float vn = quad_perm<0x00>(v), vt = quad_perm<0xA5>(v);
       const float mc = act ? mu(c) : 0.f;
       if (act) f(4 * c + q, vn + ((q & 1) ? -mc : mc) * vt);
@@ -149,7 +160,7 @@ struct RegRows {
       else unit = !act;
       float v = sg * from_dof(x, dof);
       if (m.neqrow > 0) {
-        const float vd = j_dot(act ? 3 * ncon + k : 0, xr);
+        const float vd = j_dot<FINE>(act ? 3 * ncon + k : 0, xr);
         v = unit ? v : vd;
       }
       if (act) f(4 * ncon + k, v);
@@ -404,29 +415,23 @@ DEV void newton_reg(const DevModel& m, float* W0, const Team& t0, int& status, i
   load_row<NB>(R.W + m.o_M, i, nv, Mrow);
   R.clear_units();  // (the poses and motion subspaces there are dead from here on)
   // ---- start point: cost of the warm start vs cost of a0
-  float Mr = row_dot<NB>(Mrow, rep_dof<T>(a - a0));
+  const float Mw = row_dot<NB>(Mrow, rep_dof<T>(a - a0));
   float cw = 0.f, c0 = 0.f;
   auto cost = [&](int r, float v) {
     return FR ? row_cost(D(r), fl(r), v) : (v < 0.f ? 0.5f * D(r) * v * v : 0.f);
   };
-  R.times(a, [&](int r, float v) {
-    v -= R.W[m.o_aref + r];
-    cw += cost(r, v);
-    e(r) = v;
-  });
-  R.times(a0, [&](int r, float v) {
-    v -= R.W[m.o_aref + r];
-    c0 += cost(r, v);
-    s(r) = v;
-  });
-  cw = t.sum(cw) + dof_sum<T>(t, 0.5f * (a - a0) * Mr);
+  R.times(a, [&](int r, float v) { cw += cost(r, v - R.W[m.o_aref + r]); });
+  R.times(a0, [&](int r, float v) { c0 += cost(r, v - R.W[m.o_aref + r]); });
+  cw = t.sum(cw) + dof_sum<T>(t, 0.5f * (a - a0) * Mw);
   c0 = t.sum(c0);
+  if (!(cw <= c0) || done) a = a0;
+  // the residuals are small differences of large terms (a stiff contact's D e is its force)
+  // and later steps only add to them: their start is summed in FP64
+  R.template times<true>(a, [&](int r, float v) { e(r) = v - R.W[m.o_aref + r]; });
   t.sync();
-  if (!(cw <= c0) || done) {
-    a = a0;
-    Mr = 0.f;
-    for (int r = t.lane; r < nrow; r += T) e(r) = s(r);
-  }
+  // the smooth part of the gradient, M (a - a0), as M a - frc: a0's own rounding, which M
+  // multiplies and which is large where a0 is (a leg pressed into the ground), stays out of it
+  float Mr = row_dot<NB>(Mrow, rep_dof<T>(a), dv ? -R.W[m.o_frc + i] : 0.f);
   t.sync();
   float gstop = 0.f;
   if (gtol > 0.f) gstop = gtol * dof_max<T>(t, fmaxf(1.f, dv ? fabsf(R.W[m.o_frc + i]) : 0.f));
