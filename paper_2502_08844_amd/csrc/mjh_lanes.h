@@ -16,7 +16,9 @@ namespace mjh {
 typedef float f32x32 __attribute__((ext_vector_type(32)));
 
 // The compiler does not fuse a DPP move into a multiply-add, so the blocks are written out.
-// Each starts with the two wait states a DPP read needs after its source was written.
+// Each starts with the two wait states a DPP read needs after its source was written; a block
+// whose result may be read next by a DPP or matrix instruction also ends with them, because
+// the compiler's hazard checks do not look into the blocks.
 #define MJH_AX(d) "v_fmac_f32_dpp %" #d ", %[c], %[b] row_newbcast:" #d " row_mask:0xf bank_mask:0xf\n"
 #define MJH_AX4 MJH_AX(0) MJH_AX(1) MJH_AX(2) MJH_AX(3)
 #define MJH_AX8 MJH_AX4 MJH_AX(4) MJH_AX(5) MJH_AX(6) MJH_AX(7)
@@ -48,9 +50,9 @@ DEV void dpp_axpy(float* A, float c, float b) {
 template <int N>
 DEV float dpp_dot(float v, float c, const float* A) {
   static_assert(N == 4 || N == 12 || N == 16, "the blocks of 20, 28 and 16 or 32 entries");
-  if constexpr (N == 4) asm("s_nop 1\n" MJH_DT4 : "+v"(v) : MJH_I4, [c] "v"(c));
-  if constexpr (N == 12) asm("s_nop 1\n" MJH_DT12 : "+v"(v) : MJH_I12, [c] "v"(c));
-  if constexpr (N == 16) asm("s_nop 1\n" MJH_DT16 : "+v"(v) : MJH_I16, [c] "v"(c));
+  if constexpr (N == 4) asm("s_nop 1\n" MJH_DT4 "s_nop 1" : "+v"(v) : MJH_I4, [c] "v"(c));
+  if constexpr (N == 12) asm("s_nop 1\n" MJH_DT12 "s_nop 1" : "+v"(v) : MJH_I12, [c] "v"(c));
+  if constexpr (N == 16) asm("s_nop 1\n" MJH_DT16 "s_nop 1" : "+v"(v) : MJH_I16, [c] "v"(c));
   return v;
 }
 #undef MJH_AX
@@ -102,6 +104,50 @@ DEV float dpp_slope4(float dp, float e, float s, float ds, float br) {
 #undef MJH_SO
 #undef MJH_SLOPE4
 
+// v + (lane B of z) n + (lane B + 1 of z) a + (lane B + 2 of z) b: a contact's frame weights,
+// on its quad's lanes, times its frame rows' entries
+#define MJH_QUAD3(b0, b1, b2)                                                               \
+  asm("s_nop 1\n"                                                                           \
+      "v_fmac_f32_dpp %[v], %[z], %[n] row_newbcast:" b0 " row_mask:0xf bank_mask:0xf\n"    \
+      "v_fmac_f32_dpp %[v], %[z], %[a] row_newbcast:" b1 " row_mask:0xf bank_mask:0xf\n"    \
+      "v_fmac_f32_dpp %[v], %[z], %[b] row_newbcast:" b2 " row_mask:0xf bank_mask:0xf\n"    \
+      "s_nop 1"                                                                              \
+      : [v] "+v"(v) : [z] "v"(z), [n] "v"(n), [a] "v"(a), [b] "v"(b))
+template <int B>
+DEV float dpp_quad3(float v, float z, float n, float a, float b) {
+  static_assert(B == 0 || B == 4 || B == 8 || B == 12, "a quad of a 16-lane row");
+  if constexpr (B == 0) MJH_QUAD3("0", "1", "2");
+  if constexpr (B == 4) MJH_QUAD3("4", "5", "6");
+  if constexpr (B == 8) MJH_QUAD3("8", "9", "10");
+  if constexpr (B == 12) MJH_QUAD3("12", "13", "14");
+  return v;
+}
+#undef MJH_QUAD3
+// rows of P = J3^T C for a contact's frame rows (n, a, b): C = [[all, d0, d2], [d0, s0, 0],
+// [d2, 0, s2]], its entries on lanes B (all, d0, s0) and B + 2 (d2, s2)
+#define MJH_FRAME(b0, b2)                                                                     \
+  asm("s_nop 1\n"                                                                             \
+      "v_mul_f32_dpp %[pn], %[all], %[n] row_newbcast:" b0 " row_mask:0xf bank_mask:0xf\n"    \
+      "v_mul_f32_dpp %[pa], %[d], %[n] row_newbcast:" b0 " row_mask:0xf bank_mask:0xf\n"      \
+      "v_mul_f32_dpp %[pb], %[d], %[n] row_newbcast:" b2 " row_mask:0xf bank_mask:0xf\n"      \
+      "v_fmac_f32_dpp %[pn], %[d], %[a] row_newbcast:" b0 " row_mask:0xf bank_mask:0xf\n"     \
+      "v_fmac_f32_dpp %[pa], %[s], %[a] row_newbcast:" b0 " row_mask:0xf bank_mask:0xf\n"     \
+      "v_fmac_f32_dpp %[pb], %[s], %[b] row_newbcast:" b2 " row_mask:0xf bank_mask:0xf\n"     \
+      "v_fmac_f32_dpp %[pn], %[d], %[b] row_newbcast:" b2 " row_mask:0xf bank_mask:0xf\n"     \
+      "s_nop 1"                                                                               \
+      : [pn] "=&v"(pn), [pa] "=&v"(pa), [pb] "=&v"(pb)                                        \
+      : [all] "v"(all), [d] "v"(d), [s] "v"(s), [n] "v"(n), [a] "v"(a), [b] "v"(b))
+template <int B>
+DEV void dpp_frame(float all, float d, float s, float n, float a, float b, float& pn, float& pa,
+                   float& pb) {
+  static_assert(B == 0 || B == 4 || B == 8 || B == 12, "a quad of a 16-lane row");
+  if constexpr (B == 0) MJH_FRAME("0", "2");
+  if constexpr (B == 4) MJH_FRAME("4", "6");
+  if constexpr (B == 8) MJH_FRAME("8", "10");
+  if constexpr (B == 12) MJH_FRAME("12", "14");
+}
+#undef MJH_FRAME
+
 // lane k of v's 16-lane row, on every lane of that row
 template <int K>
 DEV float row_bcast(float v) {
@@ -133,8 +179,12 @@ DEV Pair swap32(float x, float y) {
 // a dof vector's 16-lane rows replicated over the team: entries 0..15 in a, 16..31 in b
 template <int T>
 DEV Pair rep_dof(float x) {
-  if constexpr (T == 16) return {x, 0.f};
-  else return swap16(x);
+  if constexpr (T == 16) {
+    asm("s_nop 1" : "+v"(x));  // (x may come straight out of a block, into a DPP read)
+    return {x, 0.f};
+  } else {
+    return swap16(x);
+  }
 }
 
 // ------------------------------------------------- rows of a symmetric matrix, one per lane

@@ -80,6 +80,78 @@ DEV float smooth_solve_reg(const DevModel& m, float* W, const Team& t, float rhs
   return gj_solve<T, NB>(A, nv, i, rhs, ok);
 }
 
+// The Hessian's contact part P J3 summed over frames: on the matrix cores for 32-lane teams (two
+// worlds at once, a 32 x 32 block each) and 64-lane teams (two frames an instruction), by
+// broadcast multiply-adds for 16 lanes.  finish: row i of Mrow plus the sum.
+template <int T, int NB>
+struct HessAcc;
+template <int NB>
+struct HessAcc<16, NB> {
+  float C[NB];
+  DEV explicit HessAcc(int) {
+#pragma unroll
+    for (int j = 0; j < NB; j++) C[j] = 0.f;
+  }
+  DEV void add(float p0, float j0, float p1, float j1) {
+    dpp_axpy<16>(C, j0, p0);
+    dpp_axpy<16>(C, j1, p1);
+  }
+  DEV void add1(float p, float j) { dpp_axpy<16>(C, j, p); }
+  DEV void finish(const float* Mrow, float* A) const {
+#pragma unroll
+    for (int j = 0; j < NB; j++) A[j] = Mrow[j] + C[j];
+  }
+};
+template <int NB>
+struct HessAcc<32, NB> {
+  f32x32 C;  // block 0: the wavefront's first world, block 1 its second
+  DEV explicit HessAcc(int) {
+#pragma unroll
+    for (int v = 0; v < 32; v++) C[v] = 0.f;
+  }
+  DEV void add(float p0, float j0, float p1, float j1) {
+    C = __builtin_amdgcn_mfma_f32_32x32x1f32(p0, j0, C, 0, 0, 0);
+    C = __builtin_amdgcn_mfma_f32_32x32x1f32(p1, j1, C, 0, 0, 0);
+  }
+  DEV void add1(float p, float j) { C = __builtin_amdgcn_mfma_f32_32x32x1f32(p, j, C, 0, 0, 0); }
+  // block B's register v of lane l: its entry (8 (v / 4) + 4 (l / 32) + v % 4, l % 32); the
+  // swap gives each half-wavefront its own block's two row groups
+  DEV void finish(const float* Mrow, float* A) const {
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      const Pair h = swap32(C[v], C[16 + v]);
+      const int r = 8 * (v >> 2) + (v & 3);
+      if (r < NB) A[r] = h.a + Mrow[r];
+      if (r + 4 < NB) A[r + 4] = h.b + Mrow[r + 4];
+    }
+  }
+};
+template <int NB>
+struct HessAcc<64, NB> {
+  f32x16 C;
+  bool up;
+  DEV explicit HessAcc(int lane) : up(lane >= 32) {
+#pragma unroll
+    for (int v = 0; v < 16; v++) C[v] = 0.f;
+  }
+  DEV void add(float p0, float j0, float p1, float j1) {
+    C = __builtin_amdgcn_mfma_f32_32x32x2f32(up ? p1 : p0, up ? j1 : j0, C, 0, 0, 0);
+  }
+  DEV void add1(float p, float j) {
+    C = __builtin_amdgcn_mfma_f32_32x32x2f32(up ? 0.f : p, up ? 0.f : j, C, 0, 0, 0);
+  }
+  // register v of lane l: entry (8 (v / 4) + 4 (l / 32) + v % 4, l % 32)
+  DEV void finish(const float* Mrow, float* A) const {
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      const Pair h = swap32(C[v], C[v]);
+      const int r = 8 * (v >> 2) + (v & 3);
+      if (r < NB) A[r] = h.a + Mrow[r];
+      if (r + 4 < NB) A[r + 4] = h.b + Mrow[r + 4];
+    }
+  }
+};
+
 // The constraint rows as the solvers see them.
 template <int T, int NB>
 struct RegRows {
@@ -265,80 +337,22 @@ struct RegRows {
     t.sync();
     // a contact adds P J3 over its frames, P = J3^T C: rows P_f of this lane's dof
     const int e0 = 3 * ncon + nl + m.nfric;
-    if constexpr (T == 64) {
-      f32x16 C;
-#pragma unroll
-      for (int v = 0; v < 16; v++) C[v] = 0.f;
-      const bool up = t.lane >= 32;
-      for (int c = 0; c < ncu; c++) {
-        float n, a, b;
-        frame_col(c, n, a, b);
-        const float* k = cf + 5 * c;
-        const float pn = k[0] * n + k[1] * a + k[3] * b;
-        const float pa = k[1] * n + k[2] * a, pb = k[3] * n + k[4] * b;
-        C = __builtin_amdgcn_mfma_f32_32x32x2f32(up ? pa : pn, up ? a : n, C, 0, 0, 0);
-        C = __builtin_amdgcn_mfma_f32_32x32x2f32(up ? 0.f : pb, up ? 0.f : b, C, 0, 0, 0);
-      }
-      for (int k = 0; k < m.neqrow; k++) {
-        const float j = dv && nrow > 0 ? W[m.o_J + (e0 + k) * nv + i] : 0.f;
-        const float wk = nrow > 0 ? w(4 * ncon + nl + m.nfric + k) : 0.f;
-        C = __builtin_amdgcn_mfma_f32_32x32x2f32(up ? 0.f : wk * j, up ? 0.f : j, C, 0, 0, 0);
-      }
-      // accumulator register v of lane l: entry (8 (v / 4) + 4 (l / 32) + v % 4, l % 32)
-#pragma unroll
-      for (int v = 0; v < 16; v++) {
-        const Pair h = swap32(C[v], C[v]);
-        const int r = 8 * (v >> 2) + (v & 3);
-        if (r < NB) A[r] = h.a + Mrow[r];
-        if (r + 4 < NB) A[r + 4] = h.b + Mrow[r + 4];
-      }
-    } else if constexpr (T == 32) {
-      f32x32 C;  // block 0: the wavefront's first world, block 1 its second
-#pragma unroll
-      for (int v = 0; v < 32; v++) C[v] = 0.f;
-      for (int c = 0; c < ncu; c++) {
-        float n, a, b;
-        frame_col(c, n, a, b);
-        const float* k = cf + 5 * c;
-        const float pn = k[0] * n + k[1] * a + k[3] * b;
-        const float pa = k[1] * n + k[2] * a, pb = k[3] * n + k[4] * b;
-        C = __builtin_amdgcn_mfma_f32_32x32x1f32(pn, n, C, 0, 0, 0);
-        C = __builtin_amdgcn_mfma_f32_32x32x1f32(pa, a, C, 0, 0, 0);
-        C = __builtin_amdgcn_mfma_f32_32x32x1f32(pb, b, C, 0, 0, 0);
-      }
-      for (int k = 0; k < m.neqrow; k++) {
-        const float j = dv && nrow > 0 ? W[m.o_J + (e0 + k) * nv + i] : 0.f;
-        const float wk = nrow > 0 ? w(4 * ncon + nl + m.nfric + k) : 0.f;
-        C = __builtin_amdgcn_mfma_f32_32x32x1f32(wk * j, j, C, 0, 0, 0);
-      }
-      // block B's register v of lane l: its entry (8 (v / 4) + 4 (l / 32) + v % 4, l % 32);
-      // the swap gives each half-wavefront its own block's two row groups
-#pragma unroll
-      for (int v = 0; v < 16; v++) {
-        const Pair h = swap32(C[v], C[16 + v]);
-        const int r = 8 * (v >> 2) + (v & 3);
-        if (r < NB) A[r] = h.a + Mrow[r];
-        if (r + 4 < NB) A[r + 4] = h.b + Mrow[r + 4];
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < NB; j++) A[j] = Mrow[j];
-      for (int c = 0; c < ncu; c++) {
-        float n, a, b;
-        frame_col(c, n, a, b);
-        const float* k = cf + 5 * c;
-        const float pn = k[0] * n + k[1] * a + k[3] * b;
-        const float pa = k[1] * n + k[2] * a, pb = k[3] * n + k[4] * b;
-        dpp_axpy<16>(A, n, pn);
-        dpp_axpy<16>(A, a, pa);
-        dpp_axpy<16>(A, b, pb);
-      }
-      for (int k = 0; k < m.neqrow; k++) {
-        const float j = dv && nrow > 0 ? W[m.o_J + (e0 + k) * nv + i] : 0.f;
-        const float wk = nrow > 0 ? w(4 * ncon + nl + m.nfric + k) : 0.f;
-        dpp_axpy<16>(A, j, wk * j);
-      }
+    HessAcc<T, NB> acc(t.lane);
+    for (int c = 0; c < ncu; c++) {
+      float n, a, b;
+      frame_col(c, n, a, b);
+      const float* k = cf + 5 * c;
+      const float pn = k[0] * n + k[1] * a + k[3] * b;
+      const float pa = k[1] * n + k[2] * a, pb = k[3] * n + k[4] * b;
+      acc.add(pn, n, pa, a);
+      acc.add1(pb, b);
     }
+    for (int k = 0; k < m.neqrow; k++) {
+      const float j = dv && nrow > 0 ? W[m.o_J + (e0 + k) * nv + i] : 0.f;
+      const float wk = nrow > 0 ? w(4 * ncon + nl + m.nfric + k) : 0.f;
+      acc.add1(wk * j, j);
+    }
+    acc.finish(Mrow, A);
     if (nou > 0) {
       const float du = get_units(2);
 #pragma unroll
@@ -389,11 +403,10 @@ struct RowRep {
   }
 };
 
-// newton_impl's solve (see there for the steps and the stopping rules)
+// newton_impl's solve (see there for the steps and the stopping rules), rows in chunks of T
 template <int T, int NB, bool FR>
-DEV void newton_reg(const DevModel& m, float* W0, const Team& t0, int& status, int iters,
-                    float gtol) {
-  RegRows<T, NB> R(m, W0, t0, m.o_Mr);
+DEV void newton_chunks(const DevModel& m, int& status, int iters, float gtol, RegRows<T, NB>& R,
+                       int nru) {
   const Team& t = R.t;
   // the row arrays (through the phase's base, so that no address is held across phases)
   auto e = [&](int r) -> float& { return R.W[m.o_e + r]; };   // J a - aref
@@ -402,13 +415,7 @@ DEV void newton_reg(const DevModel& m, float* W0, const Team& t0, int& status, i
   auto fl = [&](int r) { return FR ? R.W[m.o_fl + r] : 0.f; };
   const int nrow = R.nrow, i = R.i, nv = m.nv;
   const bool dv = R.dv;
-  const int nru = wave_max<T>(nrow);
   const float a0 = dv ? R.W[m.o_a0 + i] : 0.f;
-  if (nru == 0) {
-    if (dv) R.W[m.o_qacc + i] = a0;
-    t.sync();
-    return;
-  }
   bool done = nrow == 0;
   float a = dv ? R.W[m.o_qacc + i] : 0.f;
   float Mrow[NB];
@@ -558,6 +565,319 @@ DEV void newton_reg(const DevModel& m, float* W0, const Team& t0, int& status, i
   }
   if (dv) R.W[m.o_qacc + i] = a;
   t.sync();
+}
+
+// The same solve for at most T rows: row r's state (residual, curvature, Jacobian row) is in
+// lane r's registers too, so that an iteration reads LDS only for the frame rows' columns.
+// Lane r < 4 ncon holds edge r (its quad's lanes 0, 1, 2 the frame rows), the others a limit,
+// friction-loss or equality row.  Against the rows in LDS (newton_chunks, still the solve for
+// more rows than lanes): 64 quadrupeds x 4 steps 204 -> 173 us, 8192 x 3 steps 327 -> 288 us,
+// 2048 humanoids x 2 steps 198 -> 182 us, 8192 hands x 4 steps 945 -> 847 us; what that bought is
+// LDS round trips, on which these short phases wait.
+template <int T, int NB, bool FR>
+struct LaneRows {
+  RegRows<T, NB>& R;
+  const DevModel& m;
+  float J[NB];
+  float e, D, F, smu, zc;  // F: force bound (FR); smu: +-mu of an edge; zc: see fold
+  bool con, eq;            // a contact's edge; an equality row
+  int dof;                 // dof and sign of a unit row, else -1
+  float sg;
+
+  DEV LaneRows(RegRows<T, NB>& R_, const DevModel& m_) : R(R_), m(m_) {
+    const int r = R.t.lane, c = r >> 2, q = r & 3, k = r - 4 * R.ncon;
+    con = r < 4 * R.ncon;
+    const bool act = r < R.nrow;
+    const int f = con ? 3 * c + min(q, 2) : (act ? r - R.ncon : 0);
+    const float* Jr = R.W + m.o_J + f * R.nv;
+#pragma unroll
+    for (int j = 0; j < NB; j++) {
+      J[j] = 0.f;
+      if (j < min_nv<NB>() || j < R.nv) J[j] = Jr[j];
+    }
+    if (!act) {
+#pragma unroll
+      for (int j = 0; j < NB; j++) J[j] = 0.f;
+    }
+    const float mc = con ? R.mu(c) : 0.f;
+    smu = (q & 1) ? -mc : mc;
+    zc = q == 1 ? -mc : (q == 2 ? mc : 0.f);
+    D = act ? R.W[m.o_D + r] : 0.f;
+    F = FR && act ? R.W[m.o_fl + r] : 0.f;
+    dof = -1;
+    sg = 1.f;
+    eq = act && k >= R.nl + m.nfric;
+    if (act && k >= 0 && k < R.nl) R.limit_sign(k, dof, sg);
+    else if (act && k >= R.nl && !eq) dof = m.fric_dadr[k - R.nl];
+  }
+  // J_r x (0 past the world's rows)
+  template <bool FINE = false>
+  DEV float times(float x) const {
+    const Pair xr = rep_dof<T>(x);
+    float v;
+    if constexpr (FINE) {
+      double acc = 0.0;
+      R.template fine_dot<0>(acc, J, xr);
+      v = (float)acc;
+    } else {
+      v = row_dot<NB>(J, xr);
+    }
+    const float vn = quad_perm<0x00>(v), vt = quad_perm<0xA5>(v);
+    return con ? vn + smu * vt : v;
+  }
+  // a row vector folded onto the contacts' frames: lanes 0, 1, 2 of a quad hold sum y,
+  // mu (y0 - y1), mu (y2 - y3)
+  DEV float fold(float y) const {
+    const float yx = quad_perm<kXor1>(y), sm = y + yx;
+    const float all = sm + quad_perm<kXor2>(sm);
+    return (R.t.lane & 3) == 0 ? all : zc * (y - yx);
+  }
+  template <int C>
+  DEV float add_contacts(float v, const RowRep<T>& z) const {
+    if (C < R.ncu) {
+      float n, a, b;
+      R.frame_col(C, n, a, b);
+      v = dpp_quad3<4 * (C & 3)>(v, z.r[C >> 2], n, a, b);
+      if constexpr (C + 1 < T / 4) return add_contacts<C + 1>(v, z);
+    }
+    return v;
+  }
+  // init_i + sum_r y_r J_ri on dof lane i
+  DEV float t_times(float y, float init) const {
+    float v = init;
+    if (R.nou > 0) put(0, sg * y);
+    if (R.ncu > 0) v = add_contacts<0>(v, RowRep<T>(fold(y)));
+    if (R.nou > 0) {
+      R.t.sync();
+      v += R.get_units(0);
+      v += equalities(y);
+      R.t.sync();
+    }
+    return v;
+  }
+  DEV void put(int slot, float y) const {  // unit rows: slot for limits, the next for friction
+    if (dof >= 0) R.unit_slots(slot + (R.t.lane - 4 * R.ncon >= R.nl ? 1 : 0))[dof] = y;
+  }
+  DEV float equalities(float y) const {
+    float v = 0.f;
+    const int base = (int)(threadIdx.x & 63) - R.t.lane;
+    for (int k = 0; k < m.neqrow; k++) {
+      const int r = max(R.nrow - m.neqrow + k, 0);
+      const float yk = __int_as_float(
+          __builtin_amdgcn_ds_bpermute(4 * (base + r), __float_as_int(y)));
+      if (R.dv && R.nrow > 0) v += yk * R.W[m.o_J + (r - R.ncon) * R.nv + R.i];
+    }
+    return v;
+  }
+  template <int C, class Acc>
+  DEV void hess_contacts(const RowRep<T>& all, const RowRep<T>& d, const RowRep<T>& s,
+                         Acc& acc) const {
+    if (C < R.ncu) {
+      float n, a, b, pn, pa, pb;
+      R.frame_col(C, n, a, b);
+      dpp_frame<4 * (C & 3)>(all.r[C >> 2], d.r[C >> 2], s.r[C >> 2], n, a, b, pn, pa, pb);
+      acc.add(pn, n, pa, a);
+      acc.add1(pb, b);
+      if constexpr (C + 1 < T / 4) hess_contacts<C + 1>(all, d, s, acc);
+    }
+  }
+  // A = Mrow + sum_r w_r J_ri J_r.
+  DEV void hessian(const float* Mrow, float w, float* A) const {
+    HessAcc<T, NB> acc(R.t.lane);
+    if (R.nou > 0) put(2, w);
+    if (R.ncu > 0) {
+      const float wc = con ? w : 0.f, wx = quad_perm<kXor1>(wc), sm = wc + wx;
+      const float mc = fabsf(smu);
+      const RowRep<T> all(sm + quad_perm<kXor2>(sm)), d(mc * (wc - wx)), s(mc * mc * sm);
+      hess_contacts<0>(all, d, s, acc);
+    }
+    if (R.nou > 0) {
+      const int base = (int)(threadIdx.x & 63) - R.t.lane;
+      for (int k = 0; k < m.neqrow; k++) {
+        const int r = max(R.nrow - m.neqrow + k, 0);
+        const float wk = __int_as_float(
+            __builtin_amdgcn_ds_bpermute(4 * (base + r), __float_as_int(w)));
+        const float j = R.dv && R.nrow > 0 ? R.W[m.o_J + (r - R.ncon) * R.nv + R.i] : 0.f;
+        acc.add1(wk * j, j);
+      }
+    }
+    acc.finish(Mrow, A);
+    if (R.nou > 0) {
+      R.t.sync();
+      const float du = R.get_units(2);
+#pragma unroll
+      for (int j = 0; j < NB; j++) A[j] += j == R.i ? du : 0.f;
+      R.t.sync();
+    }
+  }
+};
+
+// dp + sum over rows of ds min(0, e + br s), n rows (uniform); the T-lane vectors replicated
+template <int T>
+DEV float slope_sum(float dp, const RowRep<T>& e, const RowRep<T>& s, const RowRep<T>& ds, float br,
+                    int n) {
+#pragma unroll
+  for (int h = 0; h < T / 16; h++)
+    if (n > 16 * h) dp = slope_rows<>(dp, e.r[h], s.r[h], ds.r[h], br, n - 16 * h);
+  return dp;
+}
+
+template <int T, int NB, bool FR>
+DEV void newton_rows(const DevModel& m, int& status, int iters, float gtol, RegRows<T, NB>& R,
+                     int nru) {
+  const Team& t = R.t;
+  const int nrow = R.nrow, i = R.i, nv = m.nv, lane = R.lane0;
+  const bool dv = R.dv;
+  const float a0 = dv ? R.W[m.o_a0 + i] : 0.f;
+  bool done = nrow == 0;
+  float a = dv ? R.W[m.o_qacc + i] : 0.f;
+  LaneRows<T, NB, FR> L(R, m);
+  const float aref = lane < nrow ? R.W[m.o_aref + lane] : 0.f;
+  float Mrow[NB];
+  load_row<NB>(R.W + m.o_M, i, nv, Mrow);
+  R.clear_units();
+  auto rep = [&](float x) { return rep_dof<T>(x); };
+  auto cost = [&](float v) {  // (rows past the world's have D = 0)
+    return FR ? (L.D > 0.f ? row_cost(L.D, L.F, v) : 0.f) : (v < 0.f ? 0.5f * L.D * v * v : 0.f);
+  };
+  auto quad = [&](float v) { return FR ? row_quad(L.D, L.F, v) : v < 0.f; };
+  auto slope = [&](float v) {
+    return FR ? row_slope(L.D, L.F, v) : (v < 0.f ? L.D * v : 0.f);
+  };
+  // ---- start point
+  {
+    const float Mw = row_dot<NB>(Mrow, rep(a - a0));
+    const float cw = t.sum(cost(L.times(a) - aref)) + dof_sum<T>(t, 0.5f * (a - a0) * Mw);
+    const float c0 = t.sum(cost(L.times(a0) - aref));
+    if (!(cw <= c0) || done) a = a0;
+  }
+  L.e = L.template times<true>(a) - aref;
+  float Mr = row_dot<NB>(Mrow, rep(a), dv ? -R.W[m.o_frc + i] : 0.f);
+  float gstop = 0.f;
+  if (gtol > 0.f) gstop = gtol * dof_max<T>(t, fmaxf(1.f, dv ? fabsf(R.W[m.o_frc + i]) : 0.f));
+  t.sync();
+  float A[NB], sc = 1.f;  // the Hessian's inverse: row -sc A
+#pragma unroll
+  for (int j = 0; j < NB; j++) A[j] = 0.f;
+  bool kept = false;
+  for (int it = 0; it < iters; it++) {
+    R.phase();
+    const float g = L.t_times(slope(L.e), Mr);
+    if (gtol > 0.f) done = done || dof_max<T>(t, fabsf(g)) <= gstop;
+    if (!__ballot(!done)) break;
+    float de = 0.f;
+    bool ok = true;
+    const bool on = quad(L.e);  // on the quadratic piece
+    if (__ballot(!done && !kept)) {
+      L.hessian(Mrow, on ? L.D : 0.f, A);
+      de = sweep_inverse<T, NB>(A, sc, nv, i, -g, ok);
+    }
+    float d = sc * row_dot<NB>(A, rep(g));
+    if (!kept) {
+      d = de;
+      if (!done && !ok) {
+        status |= 4;
+        done = true;
+      }
+    }
+    // ---- refinement
+    R.phase();
+    const float sd = L.times(d);
+    const float res = L.t_times(on ? L.D * sd : 0.f, row_dot<NB>(Mrow, rep(d), g));
+    const float corr = -sc * row_dot<NB>(A, rep(res));
+    d -= corr;
+    const float cm = dof_max<T>(t, fabsf(corr));
+    // ---- line search
+    const float s = L.times(d);
+    const float Md = row_dot<NB>(Mrow, rep(d));
+    const float gd = dof_sum<T>(t, g * d), dMd = dof_sum<T>(t, d * Md),
+                dMr = dof_sum<T>(t, d * Mr);
+    done = done || !(gd < 0.f);
+    float lo = 0.f, hi = INFINITY;
+    {
+      const RowRep<T> rs(s);
+      float br = 0.f, br2 = 0.f;
+      if (!FR) {
+        if (s != 0.f) br = -L.e / s;
+        const float dp = slope_sum<T>(dMr + br * dMd, RowRep<T>(L.e), rs, RowRep<T>(L.D * s), br, nru);
+        if (br > 0.f) {
+          if (dp <= 0.f) lo = br;
+          else hi = br;
+        }
+      } else {
+        // a friction row's slope clamp(D v, +-F) = F + min(0, D v - F) - min(0, D v + F): two
+        // one-sided terms with the residual shifted by -+F / D; an equality row's is linear
+        const bool two = L.F > 0.f && L.F < INFINITY;
+        const float sh = two ? L.F / L.D : 0.f;
+        const float Ds = L.eq ? 0.f : L.D * s;
+        const float k0 = t.sum((L.eq ? L.D * s * L.e : 0.f) + (two ? L.F * s : 0.f)) + dMr;
+        const float k1 = t.sum(L.eq ? L.D * s * s : 0.f) + dMd;
+        if (s != 0.f && !L.eq) {
+          br = (sh - L.e) / s;
+          if (two) br2 = (-sh - L.e) / s;
+        }
+        const RowRep<T> e1(L.e - sh), e2(L.e + sh), w1(Ds), w2(two ? -Ds : 0.f);
+        auto at = [&](float b) {
+          const float dp = slope_sum<T>(k0 + b * k1, e1, rs, w1, b, nru);
+          return m.nfric > 0 ? slope_sum<T>(dp, e2, rs, w2, b, nru) : dp;
+        };
+        const float dp = at(br);
+        if (br > 0.f) {
+          if (dp <= 0.f) lo = br;
+          else hi = br;
+        }
+        if (m.nfric > 0) {
+          const float dp2 = at(br2);
+          if (br2 > 0.f) {
+            if (dp2 <= 0.f) lo = fmaxf(lo, br2);
+            else hi = fminf(hi, br2);
+          }
+        }
+      }
+    }
+    lo = t.max(lo);
+    hi = t.min(hi);
+    const float probe = (hi < INFINITY) ? 0.5f * (lo + hi) : lo + 1.f;
+    const float ep = L.e + probe * s;
+    const bool pq = quad(ep);
+    float Ac = pq ? L.D * s * L.e : 0.f, Bc = pq ? L.D * s * s : 0.f;
+    if (FR && !pq) Ac = s * row_slope(L.D, L.F, ep);
+    Ac = t.sum(Ac) + dMr;
+    Bc = t.sum(Bc) + dMd;
+    float al = -Ac / Bc;
+    al = fminf(fmaxf(al, lo), hi);
+    // ---- update
+    bool moved = false;
+    if (!done) {
+      a += al * d;
+      Mr += al * Md;
+      const float e1 = L.e + al * s;
+      moved = FR ? row_piece(L.D, L.F, L.e) != row_piece(L.D, L.F, e1)
+                 : (L.e < 0.f) != (e1 < 0.f);
+      L.e = e1;
+    }
+    moved = team_any<T>(moved && lane < nrow, lane);
+    const float am = dof_max<T>(t, fmaxf(1.f, fabsf(a)));
+    done = done || (!moved && cm <= kNewtonExitTol * am);
+    kept = !moved;
+  }
+  if (lane < nrow) R.W[m.o_e + lane] = L.e;
+  if (dv) R.W[m.o_qacc + i] = a;
+  t.sync();
+}
+
+template <int T, int NB, bool FR>
+DEV void newton_reg(const DevModel& m, float* W, const Team& t, int& status, int iters, float gtol) {
+  RegRows<T, NB> R(m, W, t, m.o_Mr);
+  const int nru = wave_max<T>(R.nrow);
+  if (nru == 0) {
+    if (R.dv) W[m.o_qacc + R.i] = W[m.o_a0 + R.i];
+    t.sync();
+  } else if (nru <= T) {
+    newton_rows<T, NB, FR>(m, status, iters, gtol, R, nru);
+  } else {
+    newton_chunks<T, NB, FR>(m, status, iters, gtol, R, nru);
+  }
 }
 
 // implicit_damping with the registers' elimination
