@@ -812,7 +812,10 @@ static mjh_status sync_tables(mjh_batch* b) {
     b->reg = RegShape();
     if (mix) b->reg.nb = 28;
   }
-  if (b->reg.nb) b->block = (b->block + 63) & ~63;  // whole wavefronts (team_of)
+  if (b->reg.nb) {
+    b->block = (b->block + 63) & ~63;  // whole wavefronts (team_of)
+    if (lds > kDefaultLds) MJH_HIP(allow_step_reg_lds(b->reg, b->rk4, lds));
+  }
   b->dirty = false;
   b->ptrs_dirty = false;
   if (b->graph_exec) { (void)hipGraphExecDestroy(b->graph_exec); b->graph_exec = nullptr; }
@@ -951,9 +954,16 @@ mjh_status mjh_world_alloc(mjh_ctx* ctx, const int32_t* model_ids, const int32_t
     const DevModel& d = ctx->models[gr.model]->dm;
     // default launch shape: small trees take a quarter or half of a wavefront, large
     // ones a whole one.  A whole-wavefront world is its own work-group, so the LDS of a
-    // CU can be filled one world at a time.
+    // CU can be filled one world at a time.  Smaller teams: in a batch of several models every
+    // work-group gets the largest one's threads and LDS, so groups are one wavefront (4096 mixed
+    // worlds x 2 steps 251 us, against 273 with two and 388 with four).  Alone, with at most two
+    // wavefronts a SIMD, work-groups of four put one on each SIMD of a CU (groups of two can land
+    // on the same two: 1999 worlds x 2 Runge-Kutta steps 506 against 454 us); beyond that groups
+    // of two fill a CU's LDS better (8192 worlds x 3 steps 322 against 325 us, the env step 338
+    // against 362).
     gr.team = d.nv <= 8 ? 16 : (d.nrowmax <= 32 ? 32 : 64);
-    gr.block = gr.team == 64 ? 64 : 128;
+    gr.block = gr.team == 64 || nmodel > 1 ? 64 : 128;
+    if (gr.team == 32 && nmodel == 1 && gr.nworld <= 16 * ctx->num_cu) gr.block = 256;
     b->groups.push_back(gr);
   }
   *out = b;

@@ -49,7 +49,10 @@ hipError_t launch_step(const DevGroup* groups, const DevTask* tasks, int ntask, 
 hipError_t launch_step_reg(const DevGroup* groups, const DevTask* tasks, int ntask, int nstep,
                            int block, size_t lds_bytes, bool rk4, RegShape reg,
                            hipStream_t stream);
-hipError_t set_reg_lds_limit(size_t bytes);
+// Dynamic LDS a kernel may use without asking, and the request for more (made when a batch's
+// launch shape is set, not for every instantiation when a context is created: that took 2 ms).
+constexpr size_t kDefaultLds = 65536;
+hipError_t allow_step_reg_lds(RegShape reg, bool rk4, size_t bytes);
 // Allow the step kernel `bytes` of dynamic LDS per work-group.
 hipError_t set_step_lds_limit(size_t bytes);
 // Compute body_invweight of a freshly uploaded model (one work-group).

@@ -128,9 +128,7 @@ hipError_t launch_step(const DevGroup* groups, const DevTask* tasks, int ntask, 
 }
 
 hipError_t set_step_lds_limit(size_t bytes) {
-  hipError_t e = set_reg_lds_limit(bytes);
-  if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void*)mjh_step_kernel<false, false>,
+  hipError_t e = hipFuncSetAttribute((const void*)mjh_step_kernel<false, false>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   if (e == hipSuccess)
     e = hipFuncSetAttribute((const void*)mjh_step_kernel<true, false>,

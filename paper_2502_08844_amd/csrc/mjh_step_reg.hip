@@ -57,6 +57,12 @@ hipError_t launch_step_reg(const DevGroup* groups, const DevTask* tasks, int nta
 hipError_t launch_env_reg(const DevGroup* groups, const DevTask* tasks, int ntask,
                           const EnvArgs& E, int block, size_t lds_bytes, int tab_words,
                           int ap_words, hipStream_t stream) {
+  if (lds_bytes > kDefaultLds) {
+    const hipError_t e = hipFuncSetAttribute(
+        E.dr ? (const void*)mjh_env_reg_kernel<true> : (const void*)mjh_env_reg_kernel<false>,
+        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    if (e != hipSuccess) return e;
+  }
   if (E.dr)
     hipLaunchKernelGGL((mjh_env_reg_kernel<true>), dim3(ntask), dim3(block), lds_bytes, stream,
                        groups, tasks, E, tab_words, ap_words);
@@ -66,23 +72,11 @@ hipError_t launch_env_reg(const DevGroup* groups, const DevTask* tasks, int ntas
   return hipGetLastError();
 }
 
-hipError_t set_reg_lds_limit(size_t bytes) {
-  auto allow = [&](const void* k) {
-    return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  };
-  const int shapes[6][2] = {{16, 16}, {32, 16}, {32, 20}, {64, 20}, {32, 28}, {64, 28}};
-  for (const auto& s : shapes)
-    for (int rk = 0; rk < 2; rk++) {
-      RegShape r;
-      r.team = s[0];
-      r.nb = s[1];
-      const hipError_t e = allow((const void*)step_kernel_for(r, rk != 0));
-      if (e != hipSuccess) return e;
-    }
-  hipError_t e = allow((const void*)mjh_step_mix_kernel);
-  if (e == hipSuccess) e = allow((const void*)mjh_env_reg_kernel<false>);
-  if (e == hipSuccess) e = allow((const void*)mjh_env_reg_kernel<true>);
-  return e;
+hipError_t allow_step_reg_lds(RegShape reg, bool rk4, size_t bytes) {
+  const StepRegKernel k = step_kernel_for(reg, rk4);
+  if (!k) return hipErrorInvalidValue;
+  return hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)bytes);
 }
 
 }  // namespace mjh
