@@ -534,6 +534,57 @@ mjh_status compile_model(const HostModel& h, ModelRec& rec, Packer& pk, std::str
   pk.add(invw, const_cast<const float**>(&d.body_invweight));
   std::vector<float> dof_invw(h.nv, 0.f);
   pk.add(dof_invw, const_cast<const float**>(&d.dof_invweight));
+  // packed records (mjh_model.h)
+  auto word = [](float x) { int w; std::memcpy(&w, &x, 4); return w; };
+  std::vector<int> body_rec, dof_rec, jnt_rec;
+  d.rot_id = d.jpos0 = 1;
+  int most_joints = 0;
+  for (int ib = level_start[1 < nlevel ? 1 : 0]; nlevel > 1 && ib < h.nbody; ib++) {
+    const int b = level_body[ib], j0 = body_jntadr[b], nj = body_jntnum[b];
+    most_joints = std::max(most_joints, nj);
+    int types = 0, kids = 0;
+    for (int j = 0; j < std::min(nj, 16); j++)
+      types |= (int)((unsigned)h.jnt_type[j0 + j] << (2 * j));
+    const int nch = child_start[b + 1] - child_start[b];
+    for (int c = 0; c < std::min(nch, 4); c++)
+      kids |= (int)((unsigned)(child_list[child_start[b] + c] & 255) << (8 * c));
+    const int head[12] = {b, h.body_parent[b], level[b], nj,
+                          nj ? jnt_qposadr[j0] : 0, nj ? jnt_dofadr[j0] : 0, types, j0,
+                          nch, kids, child_start[b], 0};
+    body_rec.insert(body_rec.end(), head, head + 12);
+    for (int k = 0; k < 3; k++) body_rec.push_back(word(bpos[3 * b + k]));
+    for (int k = 0; k < 9; k++) {
+      body_rec.push_back(word(body_rot[9 * b + k]));
+      if (body_rot[9 * b + k] != (k % 4 == 0 ? 1.f : 0.f)) d.rot_id = 0;
+    }
+    body_rec.push_back(word(bmass[b]));
+    for (int k = 0; k < 3; k++) body_rec.push_back(word(bipos[3 * b + k]));
+    for (int k = 0; k < 6; k++) body_rec.push_back(word(binert[6 * b + k]));
+    body_rec.insert(body_rec.end(), 2, 0);
+  }
+  for (int i = 0; i < h.nv; i++) {
+    const int a = dof_act[i];
+    const int rec[kDofRec] = {
+        word(dof_damping[i]), a, a < 0 ? 0 : h.act_type[a], word(a < 0 ? 0.f : agear[a]),
+        word(a < 0 ? 0.f : akp[a]), word(a < 0 ? 0.f : akd[a]), word(a < 0 ? 0.f : alo[a]),
+        word(a < 0 ? 0.f : ahi[a]), word(a < 0 ? 0.f : aqd[a]), a < 0 ? 0 : act_qadr[a],
+        word(dof_armature[i]), dof_body[i], 0, 0, 0, 0};
+    dof_rec.insert(dof_rec.end(), rec, rec + kDofRec);
+  }
+  for (int j = 0; j < h.njnt; j++) {
+    const int rec[kJntRec] = {h.jnt_type[j], jnt_qposadr[j], jnt_dofadr[j], 0,
+                              word(jaxis[3 * j]), word(jaxis[3 * j + 1]), word(jaxis[3 * j + 2]), 0};
+    jnt_rec.insert(jnt_rec.end(), rec, rec + kJntRec);
+    for (int k = 0; k < 3; k++)
+      if (jpos[3 * j + k] != 0.f) d.jpos0 = 0;
+  }
+  // what the records hold: body numbers of 8 bits, 16 joints a body; and the joints' rotations
+  // fit the scratch they borrow
+  d.lane_sweep = h.nbody > 1 && h.nbody <= 256 && most_joints <= 16 && h.nv > 0 &&
+                 12 * h.njnt <= 16 * h.nbody + 6 * h.nv;
+  pk.add(body_rec, &d.body_rec);
+  pk.add(dof_rec, &d.dof_rec);
+  pk.add(jnt_rec, &d.jnt_rec);
   // on-chip layout in 4-byte words, regions packed back to back (every LDS access is a
   // scalar 32-bit one, so no region needs more alignment)
   int off = 0;

@@ -35,6 +35,15 @@ constexpr int kEqSc = 24;       // adjoint scratch per equality: two anchors' an
 constexpr int kConSc = 28;      // adjoint scratch per contact: four (cotangent, body point)
                                 // pairs, the two bodies, a flag
 
+// packed constants of one body, dof or joint, in words (integers stored as such):
+// body (in level order, the world left out): body, parent, level, joints | qpos and dof address,
+//   joint types (2 bits each), first joint | children, their numbers (8 bits each, the first
+//   four), offset in child_list, 0 | pos[3], rot[9] | mass, ipos[3], inertia[6], 0, 0
+// dof: damping, actuator (-1: none), its type, gear | kp, kd, control range | default position,
+//   qpos address, armature, body | 0 x 4
+// joint: type, qpos address, dof address, 0 | axis[3], 0
+constexpr int kBodyRec = 36, kDofRec = 16, kJntRec = 8;
+
 struct DevModel {
   // ---- sizes
   int nbody, njnt, nq, nv, nu, ngeom, npair, ncand, nconmax, nlim, nfric, neq, nrowmax;
@@ -50,6 +59,9 @@ struct DevModel {
                  // 3c + 2, its edges rows 4c .. 4c + 3 of the per-row arrays, and a
                  // non-contact row r >= 4 ncon is J row r - ncon.
   int iterations, nlevel, nmpair, ntri;
+  int lane_sweep;  // the packed records hold the model: one body per lane (sweeps_lanes)
+  int rot_id;      // every body's rotation in its parent is the identity
+  int jpos0;       // every joint is at its body's origin
   int nsimple, ncapbox, nhfpair;  // pair counts of the three searches of collide_candidates
   int implicit;  // 1: joint damping and PD velocity gains integrated implicitly;
                  // 2: also the PD position gains
@@ -61,6 +73,9 @@ struct DevModel {
   float dmin, dmax, width, mid, power;  // impedance (solimp)
   float grav[3];
   // ---- int tables
+  const int* body_rec;      // [nbody - 1][kBodyRec]
+  const int* dof_rec;       // [nv][kDofRec]
+  const int* jnt_rec;       // [njnt][kJntRec]
   const int* body_parent;
   const int* body_jntadr;
   const int* body_jntnum;
