@@ -68,14 +68,11 @@ DEV void inertia_cot(float* ib, const float* g, const float* mv) {
 // impedance d(r) and its derivative
 DEV void impedance_d(const DevModel& m, float r, float& d, float& dd) {
   const float x = fminf(fabsf(r) / m.width, 1.f);
-  float y, yp;
-  if (x <= m.mid) {
-    y = powf(x, m.power) / powf(m.mid, m.power - 1.f);
-    yp = m.power * powf(x, m.power - 1.f) / powf(m.mid, m.power - 1.f);
-  } else {
-    y = 1.f - powf(1.f - x, m.power) / powf(1.f - m.mid, m.power - 1.f);
-    yp = m.power * powf(1.f - x, m.power - 1.f) / powf(1.f - m.mid, m.power - 1.f);
-  }
+  const bool lower = x <= m.mid, sq = m.power == 2.f;
+  const float z = lower ? x : 1.f - x, c = lower ? m.imp_lo : m.imp_hi;
+  const float zp = (sq ? z * z : powf(z, m.power)) / c;
+  const float y = lower ? zp : 1.f - zp;
+  const float yp = m.power * (sq ? z : powf(z, m.power - 1.f)) / c;
   d = m.dmin + y * (m.dmax - m.dmin);
   dd = (x >= 1.f) ? 0.f : (m.dmax - m.dmin) * yp * (r < 0.f ? -1.f : 1.f) / m.width;
 }

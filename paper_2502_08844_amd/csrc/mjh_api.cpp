@@ -415,13 +415,12 @@ mjh_status compile_model(const HostModel& h, ModelRec& rec, Packer& pk, std::str
   const int njrow = d.jframe ? 3 * h.nconmax + d.nlim + d.nfric + d.neqrow : d.nrowmax;
   const int nfw = d.jframe ? 5 * h.nconmax + d.nlim + d.nfric + d.neqrow : 0;
   // pairs and candidate slots
-  std::vector<int> pair_kind, pair_candadr, cand_pair;
+  std::vector<int> pair_kind, pair_candadr;
   int ncand = 0;
   for (int p = 0; p < h.npair; p++) {
     const int kind = pair_kind_of(h.geom_type[h.pair_g1[p]], h.geom_type[h.pair_g2[p]]);
     pair_kind.push_back(kind);
     pair_candadr.push_back(ncand);
-    for (int k = 0; k < pair_slots(kind); k++) cand_pair.push_back(p);
     ncand += pair_slots(kind);
   }
   d.ncand = ncand;
@@ -445,6 +444,7 @@ mjh_status compile_model(const HostModel& h, ModelRec& rec, Packer& pk, std::str
   d.B = (float)(2.0 / (dmax * tc));
   d.dmin = (float)h.solimp[0]; d.dmax = (float)h.solimp[1]; d.width = (float)h.solimp[2];
   d.mid = (float)h.solimp[3]; d.power = (float)h.solimp[4];
+  d.imp_lo = std::pow(d.mid, d.power - 1.f); d.imp_hi = std::pow(1.f - d.mid, d.power - 1.f);
   for (int k = 0; k < 3; k++) d.grav[k] = (float)h.grav[k];
   // float tables
   auto fv = [](const std::vector<double>& v) { return std::vector<float>(v.begin(), v.end()); };
@@ -480,8 +480,6 @@ mjh_status compile_model(const HostModel& h, ModelRec& rec, Packer& pk, std::str
   pk.add(h.pair_g2, &d.pair_g2);
   pk.add(pair_kind, &d.pair_kind);
   pk.add(pair_candadr, &d.pair_candadr);
-  pk.add(pair_order, &d.pair_order);
-  pk.add(cand_pair, &d.cand_pair);
   pk.add(h.act_type, &d.act_type);
   pk.add(act_qadr, &d.act_qadr);
   pk.add(act_dadr, &d.act_dadr);
@@ -521,7 +519,6 @@ mjh_status compile_model(const HostModel& h, ModelRec& rec, Packer& pk, std::str
   pk.add(gsize, &d.geom_size);
   pk.add(gpos, &d.geom_pos);
   pk.add(geom_rot, &d.geom_rot);
-  pk.add(pmu, &d.pair_mu);
   pk.add(agear, &d.act_gear);
   pk.add(akp, &d.act_kp);
   pk.add(akd, &d.act_kd);
@@ -585,6 +582,24 @@ mjh_status compile_model(const HostModel& h, ModelRec& rec, Packer& pk, std::str
   pk.add(body_rec, &d.body_rec);
   pk.add(dof_rec, &d.dof_rec);
   pk.add(jnt_rec, &d.jnt_rec);
+  std::vector<int> pair_rec, cand_rec(ncand);
+  for (int s = 0; s < h.npair; s++) {
+    const int p = pair_order[s], g[2] = {h.pair_g1[p], h.pair_g2[p]};
+    const int b1 = h.geom_body[g[0]], b2 = h.geom_body[g[1]];
+    const unsigned long long k1 = body_dofmask[b1], k2 = body_dofmask[b2];
+    const int head[8] = {pair_kind[p], pair_candadr[p], b1, b2, (int)(unsigned)(k2 & ~k1),
+                         (int)(unsigned)(k1 & ~k2), word(h.pair_condim[p] == 1 ? 0.f : pmu[p]), p};
+    pair_rec.insert(pair_rec.end(), head, head + 8);
+    for (int q : g) {
+      for (int k = 0; k < 3; k++) pair_rec.push_back(word(gpos[3 * q + k]));
+      for (int k = 0; k < 3; k++) pair_rec.push_back(word(gsize[3 * q + k]));
+      for (int k = 0; k < 9; k++) pair_rec.push_back(word(geom_rot[9 * q + k]));
+    }
+    pair_rec.insert(pair_rec.end(), 2, 0);
+    for (int k = 0; k < pair_slots(pair_kind[p]); k++) cand_rec[pair_candadr[p] + k] = s;
+  }
+  pk.add(pair_rec, &d.pair_rec);
+  pk.add(cand_rec, &d.cand_rec);
   // on-chip layout in 4-byte words, regions packed back to back (every LDS access is a
   // scalar 32-bit one, so no region needs more alignment)
   int off = 0;

@@ -104,6 +104,14 @@ struct Team {
     }
     return __int_as_float(r);
   }
+  // the team's lanes with the flag set, bit l for lane l
+  DEV unsigned long long flags(bool f) const {
+    const int base = (int)(threadIdx.x & 63) - lane;
+    const unsigned long long b = __ballot(f) >> base;
+    return T == 64 ? b : b & ((1ull << T) - 1);
+  }
+  // how many lanes before this one have the flag set, of the team's flags
+  DEV int rank(unsigned long long fl) const { return __popcll(fl & ((1ull << lane) - 1)); }
   // exclusive prefix sum over the team's lanes
   DEV int exscan(int v) const {
     int x = v;
@@ -851,23 +859,59 @@ DEV float sphere_hfield_tri(const DevModel& m, const float* xg, const float* Rg,
   return (below ? -L : L) - r;
 }
 
-// Evaluate candidate `sub` of pair `p` (kind-specific); returns dist and fills pos and
+// A pair's packed constants (kPairRec) with the geoms' positions and axes in the world.  One
+// batch of loads brings them all: from tables by pair, then geom, then body, they were chains of
+// four loads, and a contact repeated its candidate's.  With a dof per lane for the contacts'
+// Jacobians and the impedance's products: 64 quadrupeds x 3 steps 158 -> 148 us, 65536 x 1
+// 430 -> 410, 8192 hands x 4 779 -> 729.
+struct PairGeo {
+  int kind, cand, b1, b2, pair;
+  unsigned plus, minus;  // dofs that move body 2 only, body 1 only (the first 32)
+  float mu;
+  float s1[3], s2[3], q2[9], x1[3], z1[3], x2[3], z2[3];  // sizes, geom 2's rotation in body 2
+};
+DEV PairGeo load_pair(const DevModel& m, const float* W, int s) {
+  // (a base of its own, see opaque_zero: hoisted addresses spilled in the environment kernels)
+  const int4* pr = (const int4*)(m.pair_rec + kPairRec * s + opaque_zero());
+  int w[kPairRec];
+#pragma unroll
+  for (int k = 0; k < kPairRec / 4; k++) {
+    const int4 v = pr[k];
+    w[4 * k] = v.x; w[4 * k + 1] = v.y; w[4 * k + 2] = v.z; w[4 * k + 3] = v.w;
+  }
+  PairGeo g;
+  g.kind = w[0]; g.cand = w[1]; g.b1 = w[2]; g.b2 = w[3];
+  g.plus = (unsigned)w[4]; g.minus = (unsigned)w[5]; g.mu = __int_as_float(w[6]); g.pair = w[7];
+  auto f = [&](int k) { return __int_as_float(w[k]); };
+  for (int k = 0; k < 3; k++) { g.s1[k] = f(11 + k); g.s2[k] = f(26 + k); }
+  for (int k = 0; k < 9; k++) g.q2[k] = f(29 + k);
+  auto pose = [&](int b, int at, float* x, float* z) {
+    const float* xp = W + m.o_xpos + 3 * b;
+    const float* xr = W + m.o_xmat + 9 * b;
+    const float loc[3] = {f(at), f(at + 1), f(at + 2)}, az[3] = {f(at + 8), f(at + 11), f(at + 14)};
+    mv3(xr, loc, x);
+    for (int k = 0; k < 3; k++) x[k] += xp[k];
+    mv3(xr, az, z);
+  };
+  pose(g.b1, 8, g.x1, g.z1);
+  pose(g.b2, 23, g.x2, g.z2);
+  return g;
+}
+
+// Evaluate candidate `sub` of a pair (kind-specific); returns dist and fills pos and
 // normal.  For capsule-box the parameter t selects the segment point.
-DEV float pair_contact(const DevModel& m, const float* W, int p, int sub, float tpar, float* pos,
-                       float* n) {
-  const int g1 = m.pair_g1[p], g2 = m.pair_g2[p];
-  float x1[3], R1[9], x2[3], R2[9];
-  geom_pose(m, W, g1, x1, R1);
-  geom_pose(m, W, g2, x2, R2);
-  const float* s1 = m.geom_size + 3 * g1;
-  const float* s2 = m.geom_size + 3 * g2;
-  const float z1[3] = {R1[2], R1[5], R1[8]};
-  const float z2[3] = {R2[2], R2[5], R2[8]};
-  switch (m.pair_kind[p]) {
+DEV float pair_contact(const DevModel& m, const float* W, const PairGeo& g, int sub, float tpar,
+                       float* pos, float* n) {
+  const float *x1 = g.x1, *x2 = g.x2, *z1 = g.z1, *z2 = g.z2, *s1 = g.s1, *s2 = g.s2;
+  float R2[9];
+  if (g.kind == PK_PLANE_BOX || g.kind == PK_SPHERE_HFIELD || g.kind == PK_SPHERE_BOX ||
+      g.kind == PK_CAPSULE_BOX)
+    mm3(W + m.o_xmat + 9 * g.b2, g.q2, R2);
+  switch (g.kind) {
     case PK_PLANE_SPHERE:
     case PK_PLANE_CAPSULE: {
       float c[3] = {x2[0], x2[1], x2[2]};
-      if (m.pair_kind[p] == PK_PLANE_CAPSULE) {
+      if (g.kind == PK_PLANE_CAPSULE) {
         const float sg = sub == 0 ? -s2[1] : s2[1];
         for (int k = 0; k < 3; k++) c[k] += sg * z2[k];
       }
@@ -934,14 +978,13 @@ DEV void collide_candidates(const DevModel& m, float* W, const Team& t) {
   float* cd = W + m.o_cand;
   float* cp = cd + m.ncand;
   for (int s = t.lane; s < m.nsimple; s += t.T) {
-    const int p = m.pair_order[s];
-    const int base = m.pair_candadr[p];
-    const int kind = m.pair_kind[p];
+    const PairGeo g = load_pair(m, W, s);
+    const int base = g.cand, kind = g.kind;
     if (kind == PK_PLANE_BOX) {
       float dist[8];
       float pos[3], n[3];
       for (int k = 0; k < 8; k++) {
-        float d = pair_contact(m, W, p, k, 0.f, pos, n);
+        float d = pair_contact(m, W, g, k, 0.f, pos, n);
         dist[k] = d < 0.f ? d : INFINITY;
       }
       // keep the 4 deepest (ties to the lower corner)
@@ -958,41 +1001,36 @@ DEV void collide_candidates(const DevModel& m, float* W, const Team& t) {
       const int nc = kind == PK_PLANE_CAPSULE ? 2 : 1;
       float pos[3], n[3];
       for (int k = 0; k < nc; k++) {
-        float d = pair_contact(m, W, p, k, 0.f, pos, n);
+        float d = pair_contact(m, W, g, k, 0.f, pos, n);
         cd[base + k] = d < 0.f ? d : INFINITY;
         cp[base + k] = 0.f;
       }
     }
   }
   for (int s = t.lane >> 2; s < m.ncapbox; s += t.T >> 2) {  // a quad of lanes a pair
-    const int p = m.pair_order[m.nsimple + s], q = t.lane & 3;
-    const int base = m.pair_candadr[p];
-    const int g1 = m.pair_g1[p], g2 = m.pair_g2[p];
-    float x1[3], R1[9], x2[3], R2[9];
-    geom_pose(m, W, g1, x1, R1);
-    geom_pose(m, W, g2, x2, R2);
-    const float* s1 = m.geom_size + 3 * g1;
-    const float* h = m.geom_size + 3 * g2;
+    const PairGeo g = load_pair(m, W, m.nsimple + s);
+    const int base = g.cand, q = t.lane & 3;
+    const float *x1 = g.x1, *x2 = g.x2, *s1 = g.s1, *h = g.s2;
     // bounding spheres reject far pairs without changing any result
     float dc[3] = {x2[0] - x1[0], x2[1] - x1[1], x2[2] - x1[2]};
     float rb = sqrtf(h[0] * h[0] + h[1] * h[1] + h[2] * h[2]);
     float dist = INFINITY, tp = 0.f;
     if (!(sqrtf(dot3(dc, dc)) > rb + s1[1] + s1[0])) {
       float a[3], u[3];
-      for (int k = 0; k < 3; k++) { a[k] = x1[k] - s1[1] * R1[3 * k + 2]; u[k] = 2.f * s1[1] * R1[3 * k + 2]; }
+      for (int k = 0; k < 3; k++) { a[k] = x1[k] - s1[1] * g.z1[k]; u[k] = 2.f * s1[1] * g.z1[k]; }
+      float R2[9];
+      mm3(W + m.o_xmat + 9 * g.b2, g.q2, R2);
       capsule_box_quad(q, a, u, s1[0], x2, R2, h, dist, tp);
     }
     cd[base + q] = dist;
     cp[base + q] = tp;
   }
   for (int s = t.lane >> 3; s < m.nhfpair; s += t.T >> 3) {  // a half row of lanes a pair
-    const int p = m.pair_order[m.nsimple + m.ncapbox + s];
-    const int base = m.pair_candadr[p];
-    const int g1 = m.pair_g1[p], g2 = m.pair_g2[p];
-    float x1[3], R1[9], x2[3], R2[9];
-    geom_pose(m, W, g1, x1, R1);
-    geom_pose(m, W, g2, x2, R2);
-    const float r = m.geom_size[3 * g1];
+    const PairGeo g = load_pair(m, W, m.nsimple + m.ncapbox + s);
+    const int base = g.cand;
+    const float *x1 = g.x1, *x2 = g.x2, r = g.s1[0];
+    float R2[9];
+    mm3(W + m.o_xmat + 9 * g.b2, g.q2, R2);
     const int code = hfield_nearest(m, x2, R2, x1, r, t.lane & 7);
     float pos[3], n[3];
     const float d = sphere_hfield_tri(m, x2, R2, x1, r, code, pos, n);
@@ -1020,8 +1058,23 @@ DEV void contact_frame(const float* n, float* fr) {
   for (int k = 0; k < 3; k++) { fr[k] = n[k]; fr[3 + k] = t1[k]; fr[6 + k] = t2[k]; }
 }
 
+// impedance d(r) of the soft-constraint model from solimp (dmin, dmax, width, mid, power); the
+// default power of 2 takes two products where powf took half of a row's instructions
+DEV float impedance(const DevModel& m, float dist) {
+  const float x = fminf(fabsf(dist) / m.width, 1.f);
+  const bool lower = x <= m.mid;
+  const float z = lower ? x : 1.f - x;
+  const float zp = (m.power == 2.f ? z * z : powf(z, m.power)) / (lower ? m.imp_lo : m.imp_hi);
+  const float y = lower ? zp : 1.f - zp;
+  return m.dmin + y * (m.dmax - m.dmin);
+}
+
 // Phase 2: select the contacts (all penetrating candidates in slot order, or on
 // overflow the nconmax deepest, ties to the lower slot) and build their records.
+// REG (pyramids' frame rows, at most 28 dofs): also what depends on the pair alone of a contact's
+// four rows, while its record is at hand: D, the distance term of aref (in o_e) and the dofs
+// (in o_s); those words are free until Newton.
+template <bool REG = false>
 DEV void select_contacts(const DevModel& m, float* W, const Team& t, int& status,
                          const float* dr = nullptr) {
   const float* cd = W + m.o_cand;
@@ -1029,9 +1082,11 @@ DEV void select_contacts(const DevModel& m, float* W, const Team& t, int& status
   float* con = W + m.o_con;
   int* scal = (int*)(W + m.o_scal);
   // count penetrating candidates
-  int cnt = 0;
-  for (int c = t.lane; c < m.ncand; c += t.T) cnt += cd[c] < INFINITY;
-  const int total = t.isum(cnt);
+  int total = 0;
+  for (int c0 = 0; c0 < m.ncand; c0 += t.T) {
+    const int c = c0 + t.lane;
+    total += __popcll(t.flags(c < m.ncand && cd[c] < INFINITY));
+  }
   const bool overflow = total > m.nconmax;
   if (overflow) status |= 2;
   int base = 0;
@@ -1050,39 +1105,44 @@ DEV void select_contacts(const DevModel& m, float* W, const Team& t, int& status
         sel = rank < m.nconmax;
       }
     }
-    const int slot = base + t.exscan(sel ? 1 : 0);
+    const unsigned long long fl = t.flags(sel);
+    const int slot = base + t.rank(fl);
     if (sel) {
-      const int p = m.cand_pair[c];
-      const int sub = c - m.pair_candadr[p];
+      const PairGeo g = load_pair(m, W, m.cand_rec[c]);
+      const float w12 = REG ? m.body_invweight[g.b1] + m.body_invweight[g.b2] : 0.f;
+      const int sub = c - g.cand;
       float pos[3], n[3];
-      const float dist = pair_contact(m, W, p, sub, cp[c], pos, n);
+      const float dist = pair_contact(m, W, g, sub, cp[c], pos, n);
       float* r = con + kConRec * slot;
       r[0] = dist;
       r[1] = pos[0]; r[2] = pos[1]; r[3] = pos[2];
       contact_frame(n, r + 4);
       // a frictionless pair keeps four rows, all along the normal (mu = 0)
-      r[13] = m.pair_condim[p] == 1 ? 0.f : (dr ? m.pair_mu[p] * dr[kDrFric] : m.pair_mu[p]);
-      r[14] = __int_as_float(m.geom_body[m.pair_g1[p]]);
-      r[15] = __int_as_float(m.geom_body[m.pair_g2[p]]);
-      r[16] = __int_as_float(p);
+      const float mu = dr ? g.mu * dr[kDrFric] : g.mu;
+      r[13] = mu;
+      r[14] = __int_as_float(g.b1);
+      r[15] = __int_as_float(g.b2);
+      r[16] = __int_as_float(g.pair);
       r[17] = __int_as_float(sub);
+      if (REG) {
+        const float imp = impedance(m, dist);
+        const float D = imp / ((1.f - imp) * fmaxf((1.f + mu * mu) * w12, 1e-15f));
+        const float kd = m.K * imp * dist;
+        for (int k = 0; k < 4; k++) {
+          W[m.o_D + 4 * slot + k] = D;
+          W[m.o_e + 4 * slot + k] = kd;
+        }
+        W[m.o_s + 4 * slot] = __int_as_float((int)g.plus);
+        W[m.o_s + 4 * slot + 1] = __int_as_float((int)g.minus);
+      }
     }
-    base += t.isum(sel ? 1 : 0);
+    base += __popcll(fl);
   }
   if (t.lane == 0) scal[SC_NCON] = base;
   t.sync();
 }
 
 // ------------------------------------------------------------- A8: constraint rows
-// impedance d(r) of the soft-constraint model from solimp (dmin, dmax, width, mid, power)
-DEV float impedance(const DevModel& m, float dist) {
-  const float x = fminf(fabsf(dist) / m.width, 1.f);
-  float y;
-  if (x <= m.mid) y = powf(x, m.power) / powf(m.mid, m.power - 1.f);
-  else y = 1.f - powf(1.f - x, m.power) / powf(1.f - m.mid, m.power - 1.f);
-  return m.dmin + y * (m.dmax - m.dmin);
-}
-
 // rows with a per-row force bound (friction loss, equalities): the bound array exists
 DEV bool has_bounds(const DevModel& m) { return m.nfric + m.neq > 0; }
 
@@ -1138,6 +1198,10 @@ DEV void limit_row(const DevModel& m, const float* W, int code, int& dof, float&
 // R = (1-d)/d (w1 + w2); a weld adds three rotational rows, J = J_w(b1) - J_w(b2) per
 // world axis with r its rotation residual (weld_residual) and the same R.  Writes the
 // row count to the SC_NROW slot.
+// REG: contacts come with D, distance term and dofs (select_contacts); a lane keeps its dof over
+// the contacts, and aref is left as -K d(r) r: the solve, which has the rows in registers, adds
+// -B (J qvel).
+template <bool REG = false>
 DEV void constraint_rows(const DevModel& m, float* W, const Team& t) {
   int* scal = (int*)(W + m.o_scal);
   const int ncon = scal[SC_NCON];
@@ -1192,7 +1256,27 @@ DEV void constraint_rows(const DevModel& m, float* W, const Team& t) {
     scal[SC_NROW] = nrow;
     scal[SC_NRC] = nrc;
   }
-  for (int idx = t.lane; idx < ncon * nv; idx += t.T) {
+  if (REG) {
+    const int i = t.T == 64 ? t.lane & 31 : t.lane, step = t.T == 64 ? 2 : 1;
+    if (i < nv) {
+      float S[6];
+      for (int k = 0; k < 6; k++) S[k] = cdof[6 * i + k];
+      for (int c = t.T == 64 ? t.lane >> 5 : 0; c < ncon; c += step) {
+        const float* r = con + kConRec * c;
+        const unsigned plus = (unsigned)__float_as_int(W[m.o_s + 4 * c]);
+        const unsigned minus = (unsigned)__float_as_int(W[m.o_s + 4 * c + 1]);
+        const float sg = plus >> i & 1 ? 1.f : (minus >> i & 1 ? -1.f : 0.f);
+        float wx[3], jd[3];
+        cross3(S, r + 1, wx);
+        for (int k = 0; k < 3; k++) jd[k] = sg == 0.f ? 0.f : sg * (S[3 + k] + wx[k]);
+        float* Jr = J + 3 * c * nv + i;
+        Jr[0] = dot3(r + 4, jd);
+        Jr[nv] = dot3(r + 7, jd);
+        Jr[2 * nv] = dot3(r + 10, jd);
+      }
+    }
+  }
+  for (int idx = t.lane; !REG && idx < ncon * nv; idx += t.T) {
     const int c = idx / nv, i = idx - c * nv;
     const float* r = con + kConRec * c;
     const int b1 = __float_as_int(r[14]), b2 = __float_as_int(r[15]);
@@ -1298,7 +1382,12 @@ DEV void constraint_rows(const DevModel& m, float* W, const Team& t) {
   float* D = W + m.o_D;
   // frame-row contacts: the rows' J qvel from their frames' products, staged in o_fw
   float* pf = W + m.o_fw;
-  if (m.jframe) {
+  if (REG) {
+    for (int row = t.lane; row < nrc; row += t.T) {
+      aref[row] = -W[m.o_e + row];
+      if (has_bounds(m)) W[m.o_fl + row] = 0.f;
+    }
+  } else if (m.jframe) {
     for (int f = t.lane; f < nrow - ncon; f += t.T) {
       float v = 0.f;
       for (int i = 0; i < nv; i++) v += J[f * nv + i] * qvel[i];
@@ -1306,9 +1395,9 @@ DEV void constraint_rows(const DevModel& m, float* W, const Team& t) {
     }
     t.sync();
   }
-  for (int row = t.lane; row < nrow; row += t.T) {
+  for (int row = (REG ? nrc : 0) + t.lane; row < nrow; row += t.T) {
     float dist, jv = 0.f, A;
-    if (row < nrc) {
+    if (!REG && row < nrc) {
       int c = m.con_nr ? row / m.con_nr : 0;  // con_nr rows a contact when uniform
       if (!m.con_nr)
         while (c + 1 < ncon && (__float_as_int(con[kConRec * (c + 1) + 17]) >> 8) <= row) c++;
@@ -1361,7 +1450,9 @@ DEV void constraint_rows(const DevModel& m, float* W, const Team& t) {
       } else {
         dist = weld_residual(m, W, q, k - 3);
       }
-      if (m.jframe) {
+      if (REG) {
+        jv = 0.f;
+      } else if (m.jframe) {
         jv = pf[row - ncon];
       } else {
         for (int i = 0; i < nv; i++) jv += J[row * nv + i] * qvel[i];
@@ -1369,7 +1460,7 @@ DEV void constraint_rows(const DevModel& m, float* W, const Team& t) {
       A = m.body_invweight[m.eq_body[2 * q]] + m.body_invweight[m.eq_body[2 * q + 1]];
     }
     const float imp = impedance(m, dist);
-    aref[row] = -m.B * jv - m.K * imp * dist;
+    aref[row] = REG ? -(m.K * imp * dist) : -m.B * jv - m.K * imp * dist;
     D[row] = imp / ((1.f - imp) * fmaxf(A, 1e-15f));
     if (has_bounds(m))
       W[m.o_fl + row] = row < nrf ? 0.f : (row < nre ? m.fric_loss[row - nrf] : INFINITY);
@@ -2820,12 +2911,12 @@ DEV void world_step(const DevModel& m, float* W0, const Team& t0, const float* c
   {
     MJH_PHASE_CTX
     collide_candidates(m, W, t);
-    select_contacts(m, W, t, status, dr);
+    select_contacts<(NB > 0)>(m, W, t, status, dr);
     MJH_MARK(4);
   }
   {
     MJH_PHASE_CTX
-    constraint_rows(m, W, t);
+    constraint_rows<(NB > 0)>(m, W, t);
     MJH_MARK(5);
   }
   {

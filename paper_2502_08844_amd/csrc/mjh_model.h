@@ -42,7 +42,10 @@ constexpr int kConSc = 28;      // adjoint scratch per contact: four (cotangent,
 // dof: damping, actuator (-1: none), its type, gear | kp, kd, control range | default position,
 //   qpos address, armature, body | 0 x 4
 // joint: type, qpos address, dof address, 0 | axis[3], 0
-constexpr int kBodyRec = 36, kDofRec = 16, kJntRec = 8;
+// pair (in search order): kind, first candidate slot, bodies | dofs that move body 2 only, body 1
+//   only (the first 32), friction (0: frictionless), pair | geom 1: pos[3], size[3], rot[9],
+//   geom 2's the same, 0, 0
+constexpr int kBodyRec = 36, kDofRec = 16, kJntRec = 8, kPairRec = 40;
 
 struct DevModel {
   // ---- sizes
@@ -71,6 +74,7 @@ struct DevModel {
   // ---- constants
   float dt, K, B;                       // soft-constraint stiffness/damping
   float dmin, dmax, width, mid, power;  // impedance (solimp)
+  float imp_lo, imp_hi;  // mid^(power - 1), (1 - mid)^(power - 1)
   float grav[3];
   // ---- int tables
   const int* body_rec;      // [nbody - 1][kBodyRec]
@@ -102,9 +106,9 @@ struct DevModel {
   const int* pair_g2;
   const int* pair_kind;
   const int* pair_candadr;  // first candidate slot of each pair
-  const int* pair_order;    // pairs by search: nsimple one lane each, then ncapbox capsule-box
-                            // (four lanes each), then nhfpair heightfield (eight lanes each)
-  const int* cand_pair;     // [ncand] owning pair
+  const int* pair_rec;      // [npair][kPairRec], by search: nsimple one lane each, then ncapbox
+                            // capsule-box and nhfpair sphere-heightfield pairs
+  const int* cand_rec;      // [ncand] its pair's place in pair_rec
   const int* act_type;
   const int* act_qadr;
   const int* act_dadr;
@@ -130,7 +134,6 @@ struct DevModel {
   const float* geom_size;     // [ngeom][3]
   const float* geom_pos;      // [ngeom][3]
   const float* geom_rot;      // [ngeom][9]
-  const float* pair_mu;
   const int* pair_condim;     // [npair] 1 frictionless (1 row); 3 sliding (4 rows); 4 and
                               // torsion (6); 6 and rolling (10)
   const float* pair_mu_t;     // [npair] torsional friction coefficient (condim >= 4)

@@ -421,6 +421,9 @@ DEV void newton_chunks(const DevModel& m, int& status, int iters, float gtol, Re
   float Mrow[NB];
   load_row<NB>(R.W + m.o_M, i, nv, Mrow);
   R.clear_units();  // (the poses and motion subspaces there are dead from here on)
+  // constraint_rows leaves aref's distance term: add -B (J qvel)
+  R.times(dv ? R.W[m.o_qvel + i] : 0.f, [&](int r, float v) { R.W[m.o_aref + r] -= m.B * v; });
+  t.sync();
   // ---- start point: cost of the warm start vs cost of a0
   const float Mw = row_dot<NB>(Mrow, rep_dof<T>(a - a0));
   float cw = 0.f, c0 = 0.f;
@@ -732,7 +735,10 @@ DEV void newton_rows(const DevModel& m, int& status, int iters, float gtol, RegR
   bool done = nrow == 0;
   float a = dv ? R.W[m.o_qacc + i] : 0.f;
   LaneRows<T, NB, FR> L(R, m);
-  const float aref = lane < nrow ? R.W[m.o_aref + lane] : 0.f;
+  // constraint_rows leaves the distance term; the rows are here to add -B (J qvel)
+  const float aref = (lane < nrow ? R.W[m.o_aref + lane] : 0.f) -
+                     m.B * L.times(dv ? R.W[m.o_qvel + i] : 0.f);
+  if (lane < nrow) R.W[m.o_aref + lane] = aref;
   float Mrow[NB];
   load_row<NB>(R.W + m.o_M, i, nv, Mrow);
   R.clear_units();

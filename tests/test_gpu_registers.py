@@ -128,3 +128,26 @@ def test_rollout_gradients_of_partial_wavefronts(lib, kind, team):
         scale = np.sqrt((gv ** 2).sum(1) + (gc ** 2).sum((0, 2))) * np.sqrt(
             (dv ** 2).sum(1) + (dc ** 2).sum((0, 2)))
         assert np.all(np.abs(got - want) <= 1e-3 * scale), (got, want, scale)
+
+
+@pytest.mark.parametrize("team", [32, 64])
+@pytest.mark.parametrize("power,mid", [(1.0, 0.5), (2.0, 0.3), (2.0, 0.5), (3.0, 0.7)])
+def test_impedance_curves(lib, power, mid, team):
+    """The impedance's products (power 2) and powers, on both sides of the middle: feet from
+    just touching to deeper than the impedance width, four and no contacts in one wavefront."""
+    mjh, ctx = lib
+    m = robots.quadruped()
+    m.opt.solimp = (0.6, 0.9, 0.004, mid, power)
+    nw = 9
+    qp = np.tile(robots.quadruped_standing_qpos(m), (nw, 1))
+    qp[:, 2] -= np.linspace(-0.0005, 0.006, nw)
+    qp[nw // 2, 2] += 0.2
+    qp = inputs.f32(qp)
+    qv = inputs.f32(inputs.rng(7, 14).normal(0.0, 0.1, (nw, m.nv)))
+    u = inputs.controls("quadruped", m, nw, 1, seed=5)
+    ref = oracle.Oracle(m).step(qp.copy(), qv.copy(), None, u, nstep=1)
+    print(f"[gpu] impedance of power {power}, middle {mid} on {team} lanes", flush=True)
+    g = run_gpu(ctx, mjh, m, qp, qv, None, u, 1, team=team, block=64)
+    assert np.array_equal(g["ncon"], ref["ncon"])
+    err = np.abs(g["qacc"] - ref["qacc"]).max(1) / np.maximum(np.abs(ref["qacc"]).max(1), 9.81)
+    assert err.max() < 1e-4, err
