@@ -652,18 +652,18 @@ DEV void adjoint_step(const DevModel& m, float* W, const Team& t, const float* u
         const bool q = has_bounds(m) ? row_quad(D[r], fl[r], e[r]) : e[r] < 0.f;
         return q ? D[r] : 0.f;
       };
-      R.hessian(Mrow, weight, A);
+      SymAcc<TT, NB> S = R.hessian(Mrow, weight);
       bool ok = true;
       float sc;
       const float b = R.dv ? abar[i] : 0.f;
-      float x = sweep_inverse<TT, NB>(A, sc, nv, i, -b, ok);
+      float x = sym_solve<TT, NB>(S, t, nv, i, -b, A, sc, ok);
       // one step of refinement with H unassembled: the elimination alone leaves errors of
       // cond(H) eps |H^-1| |abar|, ten times a Cholesky solve's where the solution is small
       float* s = W + m.o_s;
       R.times(x, [&](int r, float v) { s[r] = weight(r) * v; });
       const float res = R.t_times([&](int r) { return s[r]; },
                                   row_dot<NB>(Mrow, rep_dof<TT>(x), b));
-      x += sc * row_dot<NB>(A, rep_dof<TT>(res));
+      x -= times_inverse<TT, NB>(A, sc, res);
       if (!ok) status |= 4;
       if (R.dv) mu[i] = x;
       t.sync();

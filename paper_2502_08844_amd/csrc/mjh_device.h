@@ -1045,12 +1045,13 @@ DEV void collide_candidates(const DevModel& m, float* W, const Team& t) {
 // contact frame: tangent 1 from the world axis least aligned with the normal (lowest
 // index on ties), tangent 2 = n x t1
 DEV void contact_frame(const float* n, float* fr) {
-  int ax = 0;
-  if (fabsf(n[1]) < fabsf(n[ax])) ax = 1;
-  if (fabsf(n[2]) < fabsf(n[ax])) ax = 2;
-  float en = n[ax];
+  const float a0 = fabsf(n[0]), a1 = fabsf(n[1]), a2 = fabsf(n[2]);
+  const bool y = a1 < a0, z = a2 < (y ? a1 : a0);
+  const float en = z ? n[2] : (y ? n[1] : n[0]);  // (selects: an indexed array is a stack slot)
   float t1[3] = {-en * n[0], -en * n[1], -en * n[2]};
-  t1[ax] += 1.f;
+  t1[0] += !y && !z ? 1.f : 0.f;
+  t1[1] += y && !z ? 1.f : 0.f;
+  t1[2] += z ? 1.f : 0.f;
   float inv = 1.f / sqrtf(dot3(t1, t1));
   for (int k = 0; k < 3; k++) t1[k] *= inv;
   float t2[3];

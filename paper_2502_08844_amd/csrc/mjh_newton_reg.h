@@ -50,6 +50,45 @@ DEV float dof_max(const Team& t, float v) {
   return Team{t.lane, T == 16 ? 16 : 32, t.tp}.max(v);
 }
 
+// Two reductions at once, by row and by dof: the wider steps come first and fold the two values
+// onto different rows (or halves), so that the steps within a row are shared.  A Newton iteration
+// has four such pairs, each a chain of 60 to 80 clocks: 65536 quadrupeds 415 -> 407 us, 8192 x 3
+// 254 -> 248, 2048 humanoids x 2 155 -> 140.
+template <class Op>
+DEV float row_reduce(float v, Op op) {  // over a 16-lane row
+  v = op(v, quad_perm<kXor1>(v));
+  v = op(v, quad_perm<kXor2>(v));
+  v = op(v, quad_perm<0x141>(v));  // row_half_mirror
+  return op(v, quad_perm<0x140>(v));  // row_mirror
+}
+template <class Op>
+DEV Pair reduce2_32(float x, float y, Op op) {  // over each half-wavefront
+  const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__float_as_int(x),
+                                                  (unsigned)__float_as_int(y), false, false);
+  return swap16(row_reduce(op(__int_as_float((int)h[0]), __int_as_float((int)h[1])), op));
+}
+template <int T, class Op>
+DEV Pair reduce2(float x, float y, Op op) {
+  if constexpr (T == 16) return {row_reduce(x, op), row_reduce(y, op)};
+  if constexpr (T == 32) return reduce2_32(x, y, op);
+  const Pair h = swap32(x, y);
+  const float v = row_reduce(op(h.a, h.b), op);
+  const Pair w = swap16(v);
+  const float r = op(w.a, w.b);
+  return swap32(r, r);
+}
+struct OpAdd { DEV float operator()(float a, float b) const { return a + b; } };
+struct OpMax { DEV float operator()(float a, float b) const { return fmaxf(a, b); } };
+template <int T>
+DEV Pair sum2(float x, float y) { return reduce2<T>(x, y, OpAdd()); }
+template <int T>
+DEV Pair max2(float x, float y) { return reduce2<T>(x, y, OpMax()); }
+// (a 64-lane team holds every dof on both halves)
+template <int T>
+DEV Pair dof_sum2(float x, float y) { return reduce2<T == 16 ? 16 : 32>(x, y, OpAdd()); }
+template <int T>
+DEV Pair dof_max2(float x, float y) { return reduce2<T == 16 ? 16 : 32>(x, y, OpMax()); }
+
 // row i of a packed symmetric matrix (zeros for lanes past nv and past nv in the row)
 template <int NB>
 DEV void load_row(const float* M, int i, int nv, float* A) {
@@ -63,6 +102,163 @@ DEV void load_row(const float* M, int i, int nv, float* A) {
       at += j < i ? 1 : j + 1;
     }
   }
+}
+
+// Newton's Hessian, summed up from a start (one row per lane) and the contacts' parts P J3 over
+// their frames, and then solved with.  On the matrix cores for 32-lane teams (two worlds at once, a 32 x 32 block each) and
+// 64-lane teams (two frames an instruction), by broadcast multiply-adds for 16 lanes.
+// solve: this lane's entry of H^-1 b, and the rows A for times_inverse (scale: a factor of this
+// lane).  ok: every pivot was positive.
+template <int T, int NB>
+struct SymAcc;
+template <int NB>
+struct SymAcc<16, NB> {
+  float C[NB];
+  DEV SymAcc(const float* R, int) {
+#pragma unroll
+    for (int j = 0; j < NB; j++) C[j] = R[j];
+  }
+  DEV void add(float p0, float j0, float p1, float j1) {
+    dpp_axpy<16>(C, j0, p0);
+    dpp_axpy<16>(C, j1, p1);
+  }
+  DEV void add1(float p, float j) { dpp_axpy<16>(C, j, p); }
+  DEV float solve(int nv, int i, float b, float* A, float& scale, bool& ok) {
+    const float x = sweep_inverse<16, NB>(C, scale, nv, i, b, ok);
+#pragma unroll
+    for (int j = 0; j < NB; j++) A[j] = C[j];
+    return x;
+  }
+  DEV static float times_inverse(const float* A, float scale, float x) {
+    return -scale * row_dot<NB>(A, rep_dof<16>(x));
+  }
+};
+// The elimination on the matrix cores is the symmetric sweep with every swept row and column left
+// unscaled: X_ij = -(H^-1)_ij p_i p_j off the diagonal, X_ii = 2 p_i - (H^-1)_ii p_i^2 at the
+// end, p_i the pivots.  A pivot then is one symmetric rank-one update of the other rows,
+// X -= v v^T / p (v: its row, 0 at the pivot), with no row or column to overwrite, and one
+// matrix instruction whatever the size: 10 vector instructions and 64 clocks of the matrix core
+// a pivot, against 28 (18 dofs) to 37 (28 dofs) vector instructions where each lane updated its
+// row by broadcast multiply-adds.  FP32 matrix and vector instructions do not overlap here (with
+// 65536 worlds their busy times add up to the whole), so 18 dofs gain in latency only: 64
+// quadrupeds x 3 steps 148 -> 144 us, 8192 x 3 269 -> 254, 65536 x 1 410 -> 415; 8192 hands
+// (22 dofs) x 4 730 -> 692, 2048 humanoids (27) x 2 160 -> 155.  The mass matrix, with one
+// right-hand side, stays with gj_solve's half-length updates (64 quadrupeds 3.7 thousand clocks
+// against 4.3).  Row and column 31, past every dof, carry the right-hand side.  Last dof first, as
+// in gj_solve.
+template <class Acc, int T, int NB>
+struct SweepBase {
+  template <int K>
+  DEV static void pivot(Acc& S, int nv, int i, float& pd) {
+    if (K < min_nv<NB>() || K < nv) {  // (nv is uniform)
+      const float x = S.template row<K>();
+      const float v = i == K ? 0.f : x;
+      pd = i == K ? x : pd;
+      const Pair w = swap16(x);
+      const float p = row_bcast<(K & 15)>(K < 16 ? w.a : w.b);
+      S.add1(-(v * __builtin_amdgcn_rcpf(p)), v);
+    }
+    if constexpr (K > 0) pivot<K - 1>(S, nv, i, pd);
+  }
+  DEV static float solve(Acc& S, const Team& t, int nv, int i, float b, float* A, float& scale,
+                         bool& ok) {
+    const float e31 = i == 31 ? 1.f : 0.f;
+    S.add_rhs(b, e31);
+    float pd = 1.f;
+    pivot<NB - 1>(S, nv, i, pd);
+    ok = !team_any<T>(!(pd > 0.f), t.lane);
+    scale = i < nv ? __builtin_amdgcn_rcpf(pd) : 0.f;  // (lane 31 holds the right-hand side)
+    S.rows(A);
+    return scale * S.template row<31>();
+  }
+};
+template <int NB>
+struct SymAcc<32, NB> {
+  f32x32 C;  // block 0: the wavefront's first world, block 1 its second
+  // block B's register v of lane l: its entry (8 (v / 4) + 4 (l / 32) + v % 4, l % 32); the
+  // swaps give each half-wavefront its own block's two row groups, and back
+  DEV SymAcc(const float* R, int) {
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      const int r = 8 * (v >> 2) + (v & 3);
+      const Pair h = r < NB ? swap32(R[r], r + 4 < NB ? R[r + 4] : 0.f) : Pair{0.f, 0.f};
+      C[v] = h.a;
+      C[16 + v] = h.b;
+    }
+  }
+  DEV void add(float p0, float j0, float p1, float j1) {
+    C = __builtin_amdgcn_mfma_f32_32x32x1f32(p0, j0, C, 0, 0, 0);
+    C = __builtin_amdgcn_mfma_f32_32x32x1f32(p1, j1, C, 0, 0, 0);
+  }
+  DEV void add1(float p, float j) { C = __builtin_amdgcn_mfma_f32_32x32x1f32(p, j, C, 0, 0, 0); }
+  DEV void add_rhs(float b, float e) { add(b, e, e, b); }
+  template <int K>
+  DEV float row() const {
+    constexpr int v = 4 * (K >> 3) + (K & 3);
+    const Pair h = swap32(C[v], C[16 + v]);
+    return K & 4 ? h.b : h.a;
+  }
+  DEV void rows(float* A) const {
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      const int r = 8 * (v >> 2) + (v & 3);
+      if (r < NB) {
+        const Pair h = swap32(C[v], C[16 + v]);
+        A[r] = h.a;
+        if (r + 4 < NB) A[r + 4] = h.b;
+      }
+    }
+  }
+};
+template <int NB>
+struct SymAcc<64, NB> {
+  f32x16 C;
+  bool up;
+  // register v of lane l: entry (8 (v / 4) + 4 (l / 32) + v % 4, l % 32)
+  DEV SymAcc(const float* R, int lane) : up(lane >= 32) {
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      const int r = 8 * (v >> 2) + (v & 3);
+      C[v] = r < NB ? (up ? (r + 4 < NB ? R[r + 4] : 0.f) : R[r]) : 0.f;
+    }
+  }
+  DEV void add(float p0, float j0, float p1, float j1) {
+    C = __builtin_amdgcn_mfma_f32_32x32x2f32(up ? p1 : p0, up ? j1 : j0, C, 0, 0, 0);
+  }
+  DEV void add1(float p, float j) {
+    C = __builtin_amdgcn_mfma_f32_32x32x2f32(up ? 0.f : p, up ? 0.f : j, C, 0, 0, 0);
+  }
+  DEV void add_rhs(float b, float e) { add(b, e, e, b); }
+  template <int K>
+  DEV float row() const {
+    constexpr int v = 4 * (K >> 3) + (K & 3);
+    const Pair h = swap32(C[v], C[v]);
+    return K & 4 ? h.b : h.a;
+  }
+  DEV void rows(float* A) const {
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      const int r = 8 * (v >> 2) + (v & 3);
+      if (r < NB) {
+        const Pair h = swap32(C[v], C[v]);
+        A[r] = h.a;
+        if (r + 4 < NB) A[r + 4] = h.b;
+      }
+    }
+  }
+};
+template <int T, int NB>
+DEV float sym_solve(SymAcc<T, NB>& S, const Team& t, int nv, int i, float b, float* A,
+                    float& scale, bool& ok) {
+  if constexpr (T == 16) return S.solve(nv, i, b, A, scale, ok);
+  else return SweepBase<SymAcc<T, NB>, T, NB>::solve(S, t, nv, i, b, A, scale, ok);
+}
+// this lane's entry of H^-1 x, from the rows that sym_solve left
+template <int T, int NB>
+DEV float times_inverse(const float* A, float scale, float x) {
+  if constexpr (T == 16) return SymAcc<T, NB>::times_inverse(A, scale, x);
+  // -scale (sum_j X_ij y_j - 2 p_i y_i), y = scale x
+  else return -scale * row_dot<NB>(A, rep_dof<T>(scale * x), -2.f * x);
 }
 
 // x_i = (A^-1 rhs)_i for the mass matrix in o_M, plus h diag(dof_vgain) with hgain
@@ -79,78 +275,6 @@ DEV float smooth_solve_reg(const DevModel& m, float* W, const Team& t, float rhs
   bool ok = true;
   return gj_solve<T, NB>(A, nv, i, rhs, ok);
 }
-
-// The Hessian's contact part P J3 summed over frames: on the matrix cores for 32-lane teams (two
-// worlds at once, a 32 x 32 block each) and 64-lane teams (two frames an instruction), by
-// broadcast multiply-adds for 16 lanes.  finish: row i of Mrow plus the sum.
-template <int T, int NB>
-struct HessAcc;
-template <int NB>
-struct HessAcc<16, NB> {
-  float C[NB];
-  DEV explicit HessAcc(int) {
-#pragma unroll
-    for (int j = 0; j < NB; j++) C[j] = 0.f;
-  }
-  DEV void add(float p0, float j0, float p1, float j1) {
-    dpp_axpy<16>(C, j0, p0);
-    dpp_axpy<16>(C, j1, p1);
-  }
-  DEV void add1(float p, float j) { dpp_axpy<16>(C, j, p); }
-  DEV void finish(const float* Mrow, float* A) const {
-#pragma unroll
-    for (int j = 0; j < NB; j++) A[j] = Mrow[j] + C[j];
-  }
-};
-template <int NB>
-struct HessAcc<32, NB> {
-  f32x32 C;  // block 0: the wavefront's first world, block 1 its second
-  DEV explicit HessAcc(int) {
-#pragma unroll
-    for (int v = 0; v < 32; v++) C[v] = 0.f;
-  }
-  DEV void add(float p0, float j0, float p1, float j1) {
-    C = __builtin_amdgcn_mfma_f32_32x32x1f32(p0, j0, C, 0, 0, 0);
-    C = __builtin_amdgcn_mfma_f32_32x32x1f32(p1, j1, C, 0, 0, 0);
-  }
-  DEV void add1(float p, float j) { C = __builtin_amdgcn_mfma_f32_32x32x1f32(p, j, C, 0, 0, 0); }
-  // block B's register v of lane l: its entry (8 (v / 4) + 4 (l / 32) + v % 4, l % 32); the
-  // swap gives each half-wavefront its own block's two row groups
-  DEV void finish(const float* Mrow, float* A) const {
-#pragma unroll
-    for (int v = 0; v < 16; v++) {
-      const Pair h = swap32(C[v], C[16 + v]);
-      const int r = 8 * (v >> 2) + (v & 3);
-      if (r < NB) A[r] = h.a + Mrow[r];
-      if (r + 4 < NB) A[r + 4] = h.b + Mrow[r + 4];
-    }
-  }
-};
-template <int NB>
-struct HessAcc<64, NB> {
-  f32x16 C;
-  bool up;
-  DEV explicit HessAcc(int lane) : up(lane >= 32) {
-#pragma unroll
-    for (int v = 0; v < 16; v++) C[v] = 0.f;
-  }
-  DEV void add(float p0, float j0, float p1, float j1) {
-    C = __builtin_amdgcn_mfma_f32_32x32x2f32(up ? p1 : p0, up ? j1 : j0, C, 0, 0, 0);
-  }
-  DEV void add1(float p, float j) {
-    C = __builtin_amdgcn_mfma_f32_32x32x2f32(up ? 0.f : p, up ? 0.f : j, C, 0, 0, 0);
-  }
-  // register v of lane l: entry (8 (v / 4) + 4 (l / 32) + v % 4, l % 32)
-  DEV void finish(const float* Mrow, float* A) const {
-#pragma unroll
-    for (int v = 0; v < 16; v++) {
-      const Pair h = swap32(C[v], C[v]);
-      const int r = 8 * (v >> 2) + (v & 3);
-      if (r < NB) A[r] = h.a + Mrow[r];
-      if (r + 4 < NB) A[r + 4] = h.b + Mrow[r + 4];
-    }
-  }
-};
 
 // The constraint rows as the solvers see them.
 template <int T, int NB>
@@ -315,9 +439,9 @@ struct RegRows {
     t.sync();
     return v;
   }
-  // A = Mrow + sum_r w(r) J_ri J_r. (row i of the Hessian), w the rows' weights
+  // Mrow + sum_r w(r) J_ri J_r. (row i of the Hessian), w the rows' weights
   template <class Wt>
-  DEV void hessian(const float* Mrow, Wt w, float* A) const {
+  DEV SymAcc<T, NB> hessian(const float* Mrow, Wt w) const {
     float* cf = W + m.o_fw;
     const int q = t.lane & 3;
     for (int cb = 0; cb < ncu; cb += T / 4) {
@@ -337,7 +461,11 @@ struct RegRows {
     t.sync();
     // a contact adds P J3 over its frames, P = J3^T C: rows P_f of this lane's dof
     const int e0 = 3 * ncon + nl + m.nfric;
-    HessAcc<T, NB> acc(t.lane);
+    float A[NB];
+    const float du = nou > 0 ? get_units(2) : 0.f;
+#pragma unroll
+    for (int j = 0; j < NB; j++) A[j] = Mrow[j] + (j == i ? du : 0.f);
+    SymAcc<T, NB> acc(A, t.lane);
     for (int c = 0; c < ncu; c++) {
       float n, a, b;
       frame_col(c, n, a, b);
@@ -352,13 +480,8 @@ struct RegRows {
       const float wk = nrow > 0 ? w(4 * ncon + nl + m.nfric + k) : 0.f;
       acc.add1(wk * j, j);
     }
-    acc.finish(Mrow, A);
-    if (nou > 0) {
-      const float du = get_units(2);
-#pragma unroll
-      for (int j = 0; j < NB; j++) A[j] += j == i ? du : 0.f;
-    }
     t.sync();
+    return acc;
   }
 };
 
@@ -447,7 +570,7 @@ DEV void newton_chunks(const DevModel& m, int& status, int iters, float gtol, Re
   if (gtol > 0.f) gstop = gtol * dof_max<T>(t, fmaxf(1.f, dv ? fabsf(R.W[m.o_frc + i]) : 0.f));
   auto quad = [&](int r) { return FR ? row_quad(D(r), fl(r), e(r)) : e(r) < 0.f; };
   auto rep = [&](float x) { return rep_dof<T>(x); };
-  float A[NB], sc = 1.f;  // the Hessian's inverse: row -sc A
+  float A[NB], sc = 1.f;  // the Hessian's inverse (times_inverse)
 #pragma unroll
   for (int j = 0; j < NB; j++) A[j] = 0.f;
   bool kept = false;      // A holds the inverse at the current pieces
@@ -466,22 +589,20 @@ DEV void newton_chunks(const DevModel& m, int& status, int iters, float gtol, Re
     bool ok = true;
     if (__ballot(!done && !kept)) {
       R.phase();
-      R.hessian(Mrow, [&](int r) { return quad(r) ? D(r) : 0.f; }, A);
-      de = sweep_inverse<T, NB>(A, sc, nv, i, -g, ok);
+      SymAcc<T, NB> S = R.hessian(Mrow, [&](int r) { return quad(r) ? D(r) : 0.f; });
+      de = sym_solve<T, NB>(S, t, nv, i, -g, A, sc, ok);
     }
-    float d = sc * row_dot<NB>(A, rep(g));
-    if (!kept) {
-      d = de;
-      if (!done && !ok) {
-        status |= 4;
-        done = true;
-      }
+    float d = de;
+    if (__ballot(kept)) d = kept ? -times_inverse<T, NB>(A, sc, g) : de;
+    if (!kept && !done && !ok) {
+      status |= 4;
+      done = true;
     }
     // ---- one step of iterative refinement, H applied unassembled
     R.phase();
     R.times(d, [&](int r, float v) { s(r) = quad(r) ? D(r) * v : 0.f; });
     const float res = R.t_times([&](int r) { return s(r); }, row_dot<NB>(Mrow, rep(d), g));
-    const float corr = -sc * row_dot<NB>(A, rep(res));
+    const float corr = times_inverse<T, NB>(A, sc, res);
     d -= corr;
     const float cm = dof_max<T>(t, fabsf(corr));
     // ---- line search quantities
@@ -583,24 +704,20 @@ struct LaneRows {
   const DevModel& m;
   float J[NB];
   float e, D, F, smu, zc;  // F: force bound (FR); smu: +-mu of an edge; zc: see fold
-  bool con, eq;            // a contact's edge; an equality row
+  bool con, act, eq;       // a contact's edge; a row of this world; an equality row
   int dof;                 // dof and sign of a unit row, else -1
   float sg;
 
   DEV LaneRows(RegRows<T, NB>& R_, const DevModel& m_) : R(R_), m(m_) {
     const int r = R.t.lane, c = r >> 2, q = r & 3, k = r - 4 * R.ncon;
     con = r < 4 * R.ncon;
-    const bool act = r < R.nrow;
-    const int f = con ? 3 * c + min(q, 2) : (act ? r - R.ncon : 0);
+    act = r < R.nrow;
+    const int f = con ? 3 * c + min(q, 2) : (act ? r - R.ncon : 0);  // (any words past them)
     const float* Jr = R.W + m.o_J + f * R.nv;
 #pragma unroll
     for (int j = 0; j < NB; j++) {
       J[j] = 0.f;
       if (j < min_nv<NB>() || j < R.nv) J[j] = Jr[j];
-    }
-    if (!act) {
-#pragma unroll
-      for (int j = 0; j < NB; j++) J[j] = 0.f;
     }
     const float mc = con ? R.mu(c) : 0.f;
     smu = (q & 1) ? -mc : mc;
@@ -626,7 +743,7 @@ struct LaneRows {
       v = row_dot<NB>(J, xr);
     }
     const float vn = quad_perm<0x00>(v), vt = quad_perm<0xA5>(v);
-    return con ? vn + smu * vt : v;
+    return con ? vn + smu * vt : (act ? v : 0.f);
   }
   // a row vector folded onto the contacts' frames: lanes 0, 1, 2 of a quad hold sum y,
   // mu (y0 - y1), mu (y2 - y3)
@@ -684,10 +801,20 @@ struct LaneRows {
       if constexpr (C + 1 < T / 4) hess_contacts<C + 1>(all, d, s, acc);
     }
   }
-  // A = Mrow + sum_r w_r J_ri J_r.
-  DEV void hessian(const float* Mrow, float w, float* A) const {
-    HessAcc<T, NB> acc(R.t.lane);
-    if (R.nou > 0) put(2, w);
+  // Mrow + sum_r w_r J_ri J_r.
+  DEV SymAcc<T, NB> hessian(const float* Mrow, float w) const {
+    float A[NB];
+#pragma unroll
+    for (int j = 0; j < NB; j++) A[j] = Mrow[j];
+    if (R.nou > 0) {
+      put(2, w);
+      R.t.sync();
+      const float du = R.get_units(2);
+#pragma unroll
+      for (int j = 0; j < NB; j++) A[j] += j == R.i ? du : 0.f;
+      R.t.sync();
+    }
+    SymAcc<T, NB> acc(A, R.t.lane);
     if (R.ncu > 0) {
       const float wc = con ? w : 0.f, wx = quad_perm<kXor1>(wc), sm = wc + wx;
       const float mc = fabsf(smu);
@@ -704,14 +831,7 @@ struct LaneRows {
         acc.add1(wk * j, j);
       }
     }
-    acc.finish(Mrow, A);
-    if (R.nou > 0) {
-      R.t.sync();
-      const float du = R.get_units(2);
-#pragma unroll
-      for (int j = 0; j < NB; j++) A[j] += j == R.i ? du : 0.f;
-      R.t.sync();
-    }
+    return acc;
   }
 };
 
@@ -753,16 +873,16 @@ DEV void newton_rows(const DevModel& m, int& status, int iters, float gtol, RegR
   // ---- start point
   {
     const float Mw = row_dot<NB>(Mrow, rep(a - a0));
-    const float cw = t.sum(cost(L.times(a) - aref)) + dof_sum<T>(t, 0.5f * (a - a0) * Mw);
-    const float c0 = t.sum(cost(L.times(a0) - aref));
-    if (!(cw <= c0) || done) a = a0;
+    const Pair c = sum2<T>(cost(L.times(a) - aref), cost(L.times(a0) - aref));
+    const float cw = c.a + dof_sum<T>(t, 0.5f * (a - a0) * Mw);
+    if (!(cw <= c.b) || done) a = a0;
   }
   L.e = L.template times<true>(a) - aref;
   float Mr = row_dot<NB>(Mrow, rep(a), dv ? -R.W[m.o_frc + i] : 0.f);
   float gstop = 0.f;
   if (gtol > 0.f) gstop = gtol * dof_max<T>(t, fmaxf(1.f, dv ? fabsf(R.W[m.o_frc + i]) : 0.f));
   t.sync();
-  float A[NB], sc = 1.f;  // the Hessian's inverse: row -sc A
+  float A[NB], sc = 1.f;  // the Hessian's inverse (times_inverse)
 #pragma unroll
   for (int j = 0; j < NB; j++) A[j] = 0.f;
   bool kept = false;
@@ -775,29 +895,27 @@ DEV void newton_rows(const DevModel& m, int& status, int iters, float gtol, RegR
     bool ok = true;
     const bool on = quad(L.e);  // on the quadratic piece
     if (__ballot(!done && !kept)) {
-      L.hessian(Mrow, on ? L.D : 0.f, A);
-      de = sweep_inverse<T, NB>(A, sc, nv, i, -g, ok);
+      SymAcc<T, NB> S = L.hessian(Mrow, on ? L.D : 0.f);
+      de = sym_solve<T, NB>(S, t, nv, i, -g, A, sc, ok);
     }
-    float d = sc * row_dot<NB>(A, rep(g));
-    if (!kept) {
-      d = de;
-      if (!done && !ok) {
-        status |= 4;
-        done = true;
-      }
+    float d = de;
+    if (__ballot(kept)) d = kept ? -times_inverse<T, NB>(A, sc, g) : de;
+    if (!kept && !done && !ok) {
+      status |= 4;
+      done = true;
     }
     // ---- refinement
     R.phase();
     const float sd = L.times(d);
     const float res = L.t_times(on ? L.D * sd : 0.f, row_dot<NB>(Mrow, rep(d), g));
-    const float corr = -sc * row_dot<NB>(A, rep(res));
+    const float corr = times_inverse<T, NB>(A, sc, res);
     d -= corr;
-    const float cm = dof_max<T>(t, fabsf(corr));
     // ---- line search
     const float s = L.times(d);
     const float Md = row_dot<NB>(Mrow, rep(d));
-    const float gd = dof_sum<T>(t, g * d), dMd = dof_sum<T>(t, d * Md),
-                dMr = dof_sum<T>(t, d * Mr);
+    const float gd = dof_sum<T>(t, g * d);
+    const Pair dM = dof_sum2<T>(d * Md, d * Mr);
+    const float dMd = dM.a, dMr = dM.b;
     done = done || !(gd < 0.f);
     float lo = 0.f, hi = INFINITY;
     {
@@ -841,15 +959,17 @@ DEV void newton_rows(const DevModel& m, int& status, int iters, float gtol, RegR
         }
       }
     }
-    lo = t.max(lo);
-    hi = t.min(hi);
+    const Pair lh = max2<T>(lo, -hi);
+    lo = lh.a;
+    hi = -lh.b;
     const float probe = (hi < INFINITY) ? 0.5f * (lo + hi) : lo + 1.f;
     const float ep = L.e + probe * s;
     const bool pq = quad(ep);
     float Ac = pq ? L.D * s * L.e : 0.f, Bc = pq ? L.D * s * s : 0.f;
     if (FR && !pq) Ac = s * row_slope(L.D, L.F, ep);
-    Ac = t.sum(Ac) + dMr;
-    Bc = t.sum(Bc) + dMd;
+    const Pair AB = sum2<T>(Ac, Bc);
+    Ac = AB.a + dMr;
+    Bc = AB.b + dMd;
     float al = -Ac / Bc;
     al = fminf(fmaxf(al, lo), hi);
     // ---- update
@@ -863,8 +983,8 @@ DEV void newton_rows(const DevModel& m, int& status, int iters, float gtol, RegR
       L.e = e1;
     }
     moved = team_any<T>(moved && lane < nrow, lane);
-    const float am = dof_max<T>(t, fmaxf(1.f, fabsf(a)));
-    done = done || (!moved && cm <= kNewtonExitTol * am);
+    const Pair ca = dof_max2<T>(fabsf(corr), fmaxf(1.f, fabsf(a)));
+    done = done || (!moved && ca.a <= kNewtonExitTol * ca.b);
     kept = !moved;
   }
   if (lane < nrow) R.W[m.o_e + lane] = L.e;

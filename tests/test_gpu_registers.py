@@ -151,3 +151,34 @@ def test_impedance_curves(lib, power, mid, team):
     assert np.array_equal(g["ncon"], ref["ncon"])
     err = np.abs(g["qacc"] - ref["qacc"]).max(1) / np.maximum(np.abs(ref["qacc"]).max(1), 9.81)
     assert err.max() < 1e-4, err
+
+
+@pytest.mark.parametrize("team", [16, 32, 64])
+@pytest.mark.parametrize("n", [1, 4, 15, 16, 17, 20, 21, 28])
+def test_newton_at_row_lengths(lib, n, team):
+    """Newton's elimination (on the matrix cores for 32 and 64 lanes) at every edge of the padded
+    rows, on unit rows: chains with friction loss on every joint, of which some are past their
+    limits.  A limit's D is imp / (1 - imp) <= 19 of its dof's diagonal entry, so cond(H) <= 20
+    cond(M) with M scaled to a unit diagonal (which elimination does not see), and the gate is
+    that of the chains above with it."""
+    mjh, ctx = lib
+    m = robots.hinge_chain(n, damping=0.05, limit=0.3, frictionloss=0.02)
+    for j in m.joints:
+        j.armature = 1000.0
+    m.opt.iterations = 10
+    nw = 5
+    r = inputs.rng(n, 15)
+    qp = inputs.f32(r.uniform(-0.35, 0.35, (nw, m.nq)))
+    qp[1] *= 0.5  # (no limit reached)
+    qp = inputs.f32(qp)
+    qv = inputs.f32(r.normal(0.0, 0.2, (nw, m.nv)))
+    o = oracle.Oracle(m)
+    ref = o.step(qp.copy(), qv.copy(), None, None, nstep=1)
+    print(f"[gpu] limited chain of {n} on {team} lanes", flush=True)
+    g = run_gpu(ctx, mjh, m, qp, qv, None, None, 1, team=team, block=64, contacts=False)
+    for w in range(nw):
+        M = o.forward(qp[w], qv[w], np.zeros(m.nv), None)["M"]
+        D = np.sqrt(np.diag(M))
+        cond = 20 * np.linalg.cond(M / D[:, None] / D)
+        err = np.abs(D * (g["qacc"][w] - ref["qacc"][w])).max() / np.abs(D * ref["qacc"][w]).max()
+        assert err <= 8 * max(n, 4) * EPS32 * cond, (w, err, cond)
