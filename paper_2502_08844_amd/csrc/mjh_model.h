@@ -65,7 +65,7 @@ struct DevModel {
   int lane_sweep;  // the packed records hold the model: one body per lane (sweeps_lanes)
   int rot_id;      // every body's rotation in its parent is the identity
   int jpos0;       // every joint is at its body's origin
-  int nsimple, ncapbox, nhfpair;  // pair counts of the three searches of collide_candidates
+  int nsimple, nplanebox, ncapbox, nhfpair;  // pair counts of collide_candidates' searches
   int implicit;  // 1: joint damping and PD velocity gains integrated implicitly;
                  // 2: also the PD position gains
   int rk4;       // 1: fourth-order Runge-Kutta (forward pass at four stages)
@@ -106,8 +106,8 @@ struct DevModel {
   const int* pair_g2;
   const int* pair_kind;
   const int* pair_candadr;  // first candidate slot of each pair
-  const int* pair_rec;      // [npair][kPairRec], by search: nsimple one lane each, then ncapbox
-                            // capsule-box and nhfpair sphere-heightfield pairs
+  const int* pair_rec;      // [npair][kPairRec], by search: nsimple one lane each (by kind),
+                            // nplanebox, ncapbox, then nhfpair sphere-heightfield
   const int* cand_rec;      // [ncand] its pair's place in pair_rec
   const int* act_type;
   const int* act_qadr;
