@@ -431,13 +431,9 @@ mjh_status compile_model(const HostModel& h, ModelRec& rec, Packer& pk, std::str
       if (want(pair_kind[p])) pair_order.push_back(p);
     return (int)(pair_order.size() - n0);
   };
-  auto simple = [](int k) {
+  d.nsimple = list_pairs([](int k) {
     return k != PK_PLANE_BOX && k != PK_CAPSULE_BOX && k != PK_SPHERE_HFIELD;
-  };
-  d.nsimple = list_pairs(simple);
-  // by kind: where they take two rounds of lanes, a round then meets fewer of them
-  std::stable_sort(pair_order.begin(), pair_order.end(),
-                   [&](int a, int b) { return pair_kind[a] < pair_kind[b]; });
+  });
   d.nplanebox = list_pairs([](int k) { return k == PK_PLANE_BOX; });
   d.ncapbox = list_pairs([](int k) { return k == PK_CAPSULE_BOX; });
   d.nhfpair = list_pairs([](int k) { return k == PK_SPHERE_HFIELD; });

@@ -106,7 +106,7 @@ struct DevModel {
   const int* pair_g2;
   const int* pair_kind;
   const int* pair_candadr;  // first candidate slot of each pair
-  const int* pair_rec;      // [npair][kPairRec], by search: nsimple one lane each (by kind),
+  const int* pair_rec;      // [npair][kPairRec], by search: nsimple one lane each,
                             // nplanebox, ncapbox, then nhfpair sphere-heightfield
   const int* cand_rec;      // [ncand] its pair's place in pair_rec
   const int* act_type;
