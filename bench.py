@@ -546,7 +546,7 @@ def main():
     roof = {"bound": "alu", "achieved": None, "peak": FP32_PUBLISHED_PEAK_TFLOPS,
             "unit": "TFLOP/s", "frac": None, "traffic": profiled_traffic(kind, nw, ns),
             "peak_nonpacked": round(FP32_NONPACKED_PEAK_TFLOPS, 1), "frac_nonpacked": None,
-            "kernel": "mjh_step_kernel", "kernel_ms": round(kavg, 3),
+            "kernel": "mjh_step_reg_kernel", "kernel_ms": round(kavg, 3),
             "flops_per_world_step": None, "flops_per_world_step_dense": None,
             "hbm_bytes_per_world_step": round(bytes_ws, 2),
             "hbm_frac": round(bytes_ws * nw * ns / (kavg * 1e-3) / 1e9 / HBM_PEAK_GBS, 8)}

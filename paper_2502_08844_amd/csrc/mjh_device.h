@@ -868,7 +868,7 @@ DEV float sphere_hfield_tri(const DevModel& m, const float* xg, const float* Rg,
 // A pair's packed constants (kPairRec) with the geoms' positions and axes in the world.  One
 // batch of loads brings them all: from tables by pair, then geom, then body, they were chains of
 // four loads, and a contact repeated its candidate's.  With a dof per lane for the contacts'
-// Jacobians and the impedance's products: 64 quadrupeds x 3 steps 158 -> 148 us, 65536 x 1
+// Jacobians and the impedance's products: 64 quadrupeds x 4 steps 158 -> 148 us, 65536 x 1
 // 430 -> 410, 8192 hands x 4 779 -> 729.
 struct PairGeo {
   int kind, cand, b1, b2, pair;
@@ -2862,8 +2862,8 @@ DEV void world_step(const DevModel& m, float* W0, const Team& t0, const float* c
 #define MJH_PHASE_CTX                                   \
   float* W = W0 + opaque_zero();                        \
   const Team t{t0.lane + opaque_zero(), TT ? TT : t0.T, t0.tp};
-  // one body and one dof per lane where they fit (64 quadrupeds: 175 -> 158 us a case of 3
-  // steps, 2048 humanoids 177 -> 169), else the loops over tables
+  // one body and one dof per lane where they fit (64 quadrupeds x 4 steps 175 -> 158 us,
+  // 2048 humanoids x 2 177 -> 169), else the loops over tables
   if (NB > 0 && m.lane_sweep && m.nbody - 1 <= t0.T) {
     MJH_PHASE_CTX
     sweeps_lanes(m, W, t, ctrl, dr);

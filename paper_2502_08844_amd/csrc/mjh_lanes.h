@@ -242,7 +242,8 @@ DEV float gj_solve(float* A, int nv, int i, float b, bool& ok) {
   return b * rd;
 }
 
-// The same elimination carried to the inverse (the symmetric sweep operator): after every
+// The same elimination carried to the inverse (the symmetric sweep operator), for 16-lane teams
+// (wider ones sweep on the matrix cores, mjh_newton_reg.h): after every
 // dof is swept, row i of A^-1 is -s A[.], s this lane's reciprocal pivot.  A swept row is
 // kept without its factor s, so that no lane's row needs rescaling; the broadcast column
 // takes it.  The right-hand side b rides along and comes out as A^-1 b with the accuracy of

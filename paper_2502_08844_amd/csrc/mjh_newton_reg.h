@@ -6,17 +6,17 @@
 //   - a contact's four edge rows are on the four lanes of a quad (lane r of a chunk of T rows
 //     holds edge r), so that the edges J_n +- mu J_tk of a product come from the frame rows'
 //     products by quad permutations;
-//   - H's contact part is a matrix-core contraction over the frame rows (32-lane teams: two
-//     worlds at once, one 32 x 32 block each);
+//   - H is summed on the matrix cores, a contraction over the frame rows, and eliminated there
+//     too (SymAcc; 32-lane teams: two worlds at once, one 32 x 32 block each);
 //   - limit and friction-loss rows are unit vectors: they add to one dof's gradient and to
 //     one diagonal entry;
 //   - control flow is uniform in the wavefront and every lane is active: a team that is done
 //     runs along without updating, because matrix instructions and lane swaps take all lanes.
 // The solves in LDS were bound by their serial chains: every entry of a triangular solve and
 // every four columns of a factor waited for an LDS or readlane round trip, and packed indices
-// were unranked per entry.  Measured against them: 8192 quadrupeds x 3 steps 662 -> 323 us,
-// 64 x 4 steps 530 -> 204 us, 2048 humanoids x 2 steps 491 -> 200 us, 8192 hands x 4 steps
-// 2079 -> 1120 us.
+// were unranked per entry.  Measured against them, before the other phases changed: 8192
+// quadrupeds x 3 steps 662 -> 323 us, 64 x 4 steps 530 -> 204 us, 2048 humanoids x 2 steps 491 ->
+// 200 us, 8192 hands x 4 steps 2079 -> 1120 us; with them as they are now 248, 142, 140 and 645.
 #pragma once
 
 namespace mjh {
@@ -141,7 +141,7 @@ struct SymAcc<16, NB> {
 // a pivot, against 28 (18 dofs) to 37 (28 dofs) vector instructions where each lane updated its
 // row by broadcast multiply-adds.  FP32 matrix and vector instructions do not overlap here (with
 // 65536 worlds their busy times add up to the whole), so 18 dofs gain in latency only: 64
-// quadrupeds x 3 steps 148 -> 144 us, 8192 x 3 269 -> 254, 65536 x 1 410 -> 415; 8192 hands
+// quadrupeds x 4 steps 148 -> 144 us, 8192 x 3 269 -> 254, 65536 x 1 410 -> 415; 8192 hands
 // (22 dofs) x 4 730 -> 692, 2048 humanoids (27) x 2 160 -> 155.  The mass matrix, with one
 // right-hand side, stays with gj_solve's half-length updates (64 quadrupeds 3.7 thousand clocks
 // against 4.3).  Row and column 31, past every dof, carry the right-hand side.  Last dof first, as
