@@ -10,8 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmjh.so")
 SOURCES = ["mjh_api.cpp", "mjh_kernels.hip", "mjh_step_reg.hip", "mjh_step_reg_small.hip",
-           "mjh_step_reg_medium.hip", "mjh_step_reg_large.hip", "mjh_adjoint.hip",
-           "mjh_adjoint_reg_32_20.hip", "mjh_adjoint_reg_64_20.hip", "mjh_adjoint_reg_64_28.hip"]
+           "mjh_step_reg_medium.hip", "mjh_step_reg_large.hip", "mjh_adjoint.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # -packed-fp32-ops: keep the compiler from emitting packed FP32 instructions.
 # -fno-hip-fp32-correctly-rounded-divide-sqrt: FP32 division and square root within a

@@ -1068,10 +1068,18 @@ DEV void contact_frame(const float* n, float* fr) {
   for (int k = 0; k < 3; k++) { fr[k] = n[k]; fr[3 + k] = t1[k]; fr[6 + k] = t2[k]; }
 }
 
-// impedance d(r) of the soft-constraint model from solimp (dmin, dmax, width, mid, power); the
-// default power of 2 takes two products where powf took half of a row's instructions
+// impedance d(r) of the soft-constraint model from solimp (dmin, dmax, width, mid, power).
+// REG: the default power of 2 takes two products where powf took half of a row's instructions.
+// The solves in LDS keep powf: rollouts run on them, and a last bit of a row's D can move a row
+// that ends on its switch to the switch's other side, where the gradient is another one.
+template <bool REG = false>
 DEV float impedance(const DevModel& m, float dist) {
   const float x = fminf(fabsf(dist) / m.width, 1.f);
+  if constexpr (!REG) {
+    const float y = x <= m.mid ? powf(x, m.power) / powf(m.mid, m.power - 1.f)
+                               : 1.f - powf(1.f - x, m.power) / powf(1.f - m.mid, m.power - 1.f);
+    return m.dmin + y * (m.dmax - m.dmin);
+  }
   const bool lower = x <= m.mid;
   const float z = lower ? x : 1.f - x;
   const float zp = (m.power == 2.f ? z * z : powf(z, m.power)) / (lower ? m.imp_lo : m.imp_hi);
@@ -1135,7 +1143,7 @@ DEV void select_contacts(const DevModel& m, float* W, const Team& t, int& status
       r[16] = __int_as_float(g.pair);
       r[17] = __int_as_float(sub);
       if (REG) {
-        const float imp = impedance(m, dist);
+        const float imp = impedance<true>(m, dist);
         const float D = imp / ((1.f - imp) * fmaxf((1.f + mu * mu) * w12, 1e-15f));
         const float kd = m.K * imp * dist;
         for (int k = 0; k < 4; k++) {
@@ -1469,7 +1477,7 @@ DEV void constraint_rows(const DevModel& m, float* W, const Team& t) {
       }
       A = m.body_invweight[m.eq_body[2 * q]] + m.body_invweight[m.eq_body[2 * q + 1]];
     }
-    const float imp = impedance(m, dist);
+    const float imp = impedance<REG>(m, dist);
     aref[row] = REG ? -(m.K * imp * dist) : -m.B * jv - m.K * imp * dist;
     D[row] = imp / ((1.f - imp) * fmaxf(A, 1e-15f));
     if (has_bounds(m))
@@ -2943,8 +2951,8 @@ DEV void world_step(const DevModel& m, float* W0, const Team& t0, const float* c
   {
     MJH_PHASE_CTX
     if constexpr (NB > 0) {
-      if (has_bounds(m)) newton_reg<TT, NB, true>(m, W, t, status, iters, gtol);
-      else newton_reg<TT, NB, false>(m, W, t, status, iters, gtol);
+      if (has_bounds(m)) newton_reg<TT, NB, true>(m, W, t, status, iters);
+      else newton_reg<TT, NB, false>(m, W, t, status, iters);
     } else {
       newton<CONE>(m, W, t, status, iters, gtol);
     }

@@ -281,7 +281,7 @@ template <int T, int NB>
 struct RegRows {
   const DevModel& m;
   float* const W0;
-  const int lane0, o_slots;
+  const int lane0;
   float* W;
   Team t;
   int i, nv, nrow, ncon, no, nl;  // dof of this lane; rows, contacts, others, active limits
@@ -293,10 +293,8 @@ struct RegRows {
     W = W0 + opaque_zero();
     t.lane = lane0 + opaque_zero();
   }
-  // slots: where the unit rows' per-dof words are, 4 nv (default: Newton's vectors in LDS,
-  // unused by these solves)
-  DEV RegRows(const DevModel& m_, float* W_, const Team& t_, int slots)
-      : m(m_), W0(W_), lane0(t_.lane), o_slots(slots), W(W_), t(t_) {
+  DEV RegRows(const DevModel& m_, float* W_, const Team& t_)
+      : m(m_), W0(W_), lane0(t_.lane), W(W_), t(t_) {
     const int* scal = (const int*)(W + m.o_scal);
     i = T == 64 ? t.lane & 31 : t.lane;
     nv = m.nv;
@@ -371,7 +369,8 @@ struct RegRows {
     dof = m.lim_dadr[code & 0xffff];
     sg = (code >> 16) ? -1.f : 1.f;
   }
-  DEV float* unit_slots(int which) const { return W + o_slots + which * nv; }
+  // the words of Newton's vectors in LDS are free here: per-dof slots of the unit rows
+  DEV float* unit_slots(int which) const { return W + m.o_Mr + which * nv; }
   DEV void clear_units() const {
     if (nou > 0)
       for (int k = t.lane; k < 4 * nv; k += T) unit_slots(0)[k] = 0.f;
@@ -528,8 +527,7 @@ struct RowRep {
 
 // newton_impl's solve (see there for the steps and the stopping rules), rows in chunks of T
 template <int T, int NB, bool FR>
-DEV void newton_chunks(const DevModel& m, int& status, int iters, float gtol, RegRows<T, NB>& R,
-                       int nru) {
+DEV void newton_chunks(const DevModel& m, int& status, int iters, RegRows<T, NB>& R, int nru) {
   const Team& t = R.t;
   // the row arrays (through the phase's base, so that no address is held across phases)
   auto e = [&](int r) -> float& { return R.W[m.o_e + r]; };   // J a - aref
@@ -566,8 +564,6 @@ DEV void newton_chunks(const DevModel& m, int& status, int iters, float gtol, Re
   // multiplies and which is large where a0 is (a leg pressed into the ground), stays out of it
   float Mr = row_dot<NB>(Mrow, rep_dof<T>(a), dv ? -R.W[m.o_frc + i] : 0.f);
   t.sync();
-  float gstop = 0.f;
-  if (gtol > 0.f) gstop = gtol * dof_max<T>(t, fmaxf(1.f, dv ? fabsf(R.W[m.o_frc + i]) : 0.f));
   auto quad = [&](int r) { return FR ? row_quad(D(r), fl(r), e(r)) : e(r) < 0.f; };
   auto rep = [&](float x) { return rep_dof<T>(x); };
   float A[NB], sc = 1.f;  // the Hessian's inverse (times_inverse)
@@ -580,7 +576,6 @@ DEV void newton_chunks(const DevModel& m, int& status, int iters, float gtol, Re
       const float er = e(r);
       return FR ? row_slope(D(r), fl(r), er) : (er < 0.f ? D(r) * er : 0.f);
     }, Mr);
-    if (gtol > 0.f) done = done || dof_max<T>(t, fabsf(g)) <= gstop;
     if (!__ballot(!done)) break;
     // ---- delta = -H^-1 g.  With no piece changed by the last step the inverse is that of the
     // last iteration (and comes out the same if the wavefront's other world needs a new one);
@@ -846,8 +841,7 @@ DEV float slope_sum(float dp, const RowRep<T>& e, const RowRep<T>& s, const RowR
 }
 
 template <int T, int NB, bool FR>
-DEV void newton_rows(const DevModel& m, int& status, int iters, float gtol, RegRows<T, NB>& R,
-                     int nru) {
+DEV void newton_rows(const DevModel& m, int& status, int iters, RegRows<T, NB>& R, int nru) {
   const Team& t = R.t;
   const int nrow = R.nrow, i = R.i, nv = m.nv, lane = R.lane0;
   const bool dv = R.dv;
@@ -879,8 +873,6 @@ DEV void newton_rows(const DevModel& m, int& status, int iters, float gtol, RegR
   }
   L.e = L.template times<true>(a) - aref;
   float Mr = row_dot<NB>(Mrow, rep(a), dv ? -R.W[m.o_frc + i] : 0.f);
-  float gstop = 0.f;
-  if (gtol > 0.f) gstop = gtol * dof_max<T>(t, fmaxf(1.f, dv ? fabsf(R.W[m.o_frc + i]) : 0.f));
   t.sync();
   float A[NB], sc = 1.f;  // the Hessian's inverse (times_inverse)
 #pragma unroll
@@ -889,7 +881,6 @@ DEV void newton_rows(const DevModel& m, int& status, int iters, float gtol, RegR
   for (int it = 0; it < iters; it++) {
     R.phase();
     const float g = L.t_times(slope(L.e), Mr);
-    if (gtol > 0.f) done = done || dof_max<T>(t, fabsf(g)) <= gstop;
     if (!__ballot(!done)) break;
     float de = 0.f;
     bool ok = true;
@@ -993,23 +984,23 @@ DEV void newton_rows(const DevModel& m, int& status, int iters, float gtol, RegR
 }
 
 template <int T, int NB, bool FR>
-DEV void newton_reg(const DevModel& m, float* W, const Team& t, int& status, int iters, float gtol) {
-  RegRows<T, NB> R(m, W, t, m.o_Mr);
+DEV void newton_reg(const DevModel& m, float* W, const Team& t, int& status, int iters) {
+  RegRows<T, NB> R(m, W, t);
   const int nru = wave_max<T>(R.nrow);
   if (nru == 0) {
     if (R.dv) W[m.o_qacc + R.i] = W[m.o_a0 + R.i];
     t.sync();
   } else if (nru <= T) {
-    newton_rows<T, NB, FR>(m, status, iters, gtol, R, nru);
+    newton_rows<T, NB, FR>(m, status, iters, R, nru);
   } else {
-    newton_chunks<T, NB, FR>(m, status, iters, gtol, R, nru);
+    newton_chunks<T, NB, FR>(m, status, iters, R, nru);
   }
 }
 
 // implicit_damping with the registers' elimination
 template <int T, int NB>
 DEV void implicit_damping_reg(const DevModel& m, float* W, const Team& t) {
-  const RegRows<T, NB> R(m, W, t, m.o_Mr);
+  const RegRows<T, NB> R(m, W, t);
   const float* D = W + m.o_D;
   const float* e = W + m.o_e;
   const float* fl = W + m.o_fl;
