@@ -98,11 +98,44 @@ DEV float dpp_slope4(float dp, float e, float s, float ds, float br) {
   if constexpr (B == 12) MJH_SLOPE4("12", "13", "14", "15");
   return dp;
 }
+#undef MJH_SN
+#undef MJH_SLOPE4
+
+// The same for rows with bounds of their own: dp += sum of (lane k of s) * clamp((lane k of D) *
+// ((lane k of e) + br (lane k of s)), lane k of lo, lane k of hi), the upper bound first, so that
+// a one-sided row (lo = -inf, hi = 0) whose breakpoint's product is no number adds nothing
+#define MJH_SP(n, k)                                                                   \
+  "v_mul_f32_dpp %[t" #n "], %[D], %[t" #n "] row_newbcast:" k " row_mask:0xf bank_mask:0xf\n"
+#define MJH_SQ(n, k)                                                                   \
+  "v_min_f32_dpp %[t" #n "], %[hi], %[t" #n "] row_newbcast:" k " row_mask:0xf bank_mask:0xf\n"
+#define MJH_SR(n, k)                                                                   \
+  "v_max_f32_dpp %[t" #n "], %[lo], %[t" #n "] row_newbcast:" k " row_mask:0xf bank_mask:0xf\n"
+#define MJH_CLAMP4(a, b, c, d)                                                          \
+  asm("s_nop 1\n" MJH_SL(0, a) MJH_SL(1, b) MJH_SL(2, c) MJH_SL(3, d) MJH_SM(0, a)       \
+      MJH_SM(1, b) MJH_SM(2, c) MJH_SM(3, d) MJH_SP(0, a) MJH_SP(1, b) MJH_SP(2, c)       \
+      MJH_SP(3, d) MJH_SQ(0, a) MJH_SQ(1, b) MJH_SQ(2, c) MJH_SQ(3, d) MJH_SR(0, a)       \
+      MJH_SR(1, b) MJH_SR(2, c) MJH_SR(3, d) MJH_SO(0, a) MJH_SO(1, b) MJH_SO(2, c)       \
+      MJH_SO(3, d)                                                                      \
+      : [dp] "+v"(dp), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3)    \
+      : [e] "v"(e), [s] "v"(s), [ds] "v"(s), [D] "v"(D), [lo] "v"(lo), [hi] "v"(hi),     \
+        [br] "v"(br))
+template <int B>
+DEV float dpp_clamp4(float dp, float e, float s, float D, float lo, float hi, float br) {
+  static_assert(B == 0 || B == 4 || B == 8 || B == 12, "four rows of a 16-lane row");
+  float t0, t1, t2, t3;
+  if constexpr (B == 0) MJH_CLAMP4("0", "1", "2", "3");
+  if constexpr (B == 4) MJH_CLAMP4("4", "5", "6", "7");
+  if constexpr (B == 8) MJH_CLAMP4("8", "9", "10", "11");
+  if constexpr (B == 12) MJH_CLAMP4("12", "13", "14", "15");
+  return dp;
+}
 #undef MJH_SL
 #undef MJH_SM
-#undef MJH_SN
 #undef MJH_SO
-#undef MJH_SLOPE4
+#undef MJH_SP
+#undef MJH_SQ
+#undef MJH_SR
+#undef MJH_CLAMP4
 
 // v + (lane B of z) n + (lane B + 1 of z) a + (lane B + 2 of z) b: a contact's frame weights,
 // on its quad's lanes, times its frame rows' entries

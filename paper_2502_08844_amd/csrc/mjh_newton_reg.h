@@ -840,6 +840,25 @@ DEV float slope_sum(float dp, const RowRep<T>& e, const RowRep<T>& s, const RowR
   return dp;
 }
 
+// dp + sum over rows of s clamp(D (e + br s), lo, hi), likewise
+template <int B = 0>
+DEV float clamp_rows(float dp, float e, float s, float D, float lo, float hi, float br, int n) {
+  if (n > B) {
+    dp = dpp_clamp4<B>(dp, e, s, D, lo, hi, br);
+    if constexpr (B < 12) return clamp_rows<B + 4>(dp, e, s, D, lo, hi, br, n);
+  }
+  return dp;
+}
+template <int T>
+DEV float clamp_sum(float dp, const RowRep<T>& e, const RowRep<T>& s, const RowRep<T>& D,
+                    const RowRep<T>& lo, const RowRep<T>& hi, float br, int n) {
+#pragma unroll
+  for (int h = 0; h < T / 16; h++)
+    if (n > 16 * h)
+      dp = clamp_rows<>(dp, e.r[h], s.r[h], D.r[h], lo.r[h], hi.r[h], br, n - 16 * h);
+  return dp;
+}
+
 template <int T, int NB, bool FR>
 DEV void newton_rows(const DevModel& m, int& status, int iters, RegRows<T, NB>& R, int nru) {
   const Team& t = R.t;
@@ -920,21 +939,19 @@ DEV void newton_rows(const DevModel& m, int& status, int iters, RegRows<T, NB>& 
           else hi = br;
         }
       } else {
-        // a friction row's slope clamp(D v, +-F) = F + min(0, D v - F) - min(0, D v + F): two
-        // one-sided terms with the residual shifted by -+F / D; an equality row's is linear
+        // every row's slope is clamp(D v, lo, hi): (-inf, 0) one-sided, (-F, F) friction loss,
+        // (-inf, inf) an equality row.  Clamped as it stands: written as one-sided terms shifted
+        // by +-F / D with F s summed apart, the terms cancelled and lost digits as F outgrew the
+        // forces (quadrupeds with F = 1e7: accelerations off by up to 7 %)
         const bool two = L.F > 0.f && L.F < INFINITY;
         const float sh = two ? L.F / L.D : 0.f;
-        const float Ds = L.eq ? 0.f : L.D * s;
-        const float k0 = t.sum((L.eq ? L.D * s * L.e : 0.f) + (two ? L.F * s : 0.f)) + dMr;
-        const float k1 = t.sum(L.eq ? L.D * s * s : 0.f) + dMd;
         if (s != 0.f && !L.eq) {
           br = (sh - L.e) / s;
           if (two) br2 = (-sh - L.e) / s;
         }
-        const RowRep<T> e1(L.e - sh), e2(L.e + sh), w1(Ds), w2(two ? -Ds : 0.f);
+        const RowRep<T> re(L.e), rD(L.D), rlo(L.F > 0.f ? -L.F : -INFINITY), rhi(L.F);
         auto at = [&](float b) {
-          const float dp = slope_sum<T>(k0 + b * k1, e1, rs, w1, b, nru);
-          return m.nfric > 0 ? slope_sum<T>(dp, e2, rs, w2, b, nru) : dp;
+          return clamp_sum<T>(dMr + b * dMd, re, rs, rD, rlo, rhi, b, nru);
         };
         const float dp = at(br);
         if (br > 0.f) {
