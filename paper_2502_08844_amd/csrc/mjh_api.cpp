@@ -883,7 +883,7 @@ static mjh_status sync_tables(mjh_batch* b) {
   }
   if (b->reg.nb) {
     b->block = (b->block + 63) & ~63;  // whole wavefronts (team_of)
-    if (lds > kDefaultLds) MJH_HIP(allow_step_reg_lds(b->reg, b->rk4, lds));
+    if (lds > kDefaultLds) MJH_HIP(allow_step_reg_lds(b->reg, b->rk4, ctx->lds_limit));
   }
   b->dirty = false;
   b->ptrs_dirty = false;
@@ -1141,6 +1141,8 @@ mjh_status mjh_env_step(mjh_batch* b, int32_t nenv, int32_t nsub, const float* a
   const size_t lds = b->lds_bytes + (size_t)ap_words * sizeof(float);
   if (lds > ctx->lds_limit)
     return fail(ctx, MJH_EUNSUPPORTED, "env_step: work-group exceeds the LDS limit");
+  if (lds > kDefaultLds && b->reg.nb && env_reg_shape(b->reg, b->rk4))
+    MJH_HIP(allow_env_reg_lds(params != nullptr, ctx->lds_limit));
   EnvArgs E;
   E.nenv = nenv; E.nsub = nsub; E.nobs = 12 + 3 * h.nu;
   E.action = action; E.command = command; E.reset_qpos = reset_qpos; E.reset_qvel = reset_qvel;

@@ -49,10 +49,13 @@ hipError_t launch_step(const DevGroup* groups, const DevTask* tasks, int ntask, 
 hipError_t launch_step_reg(const DevGroup* groups, const DevTask* tasks, int ntask, int nstep,
                            int block, size_t lds_bytes, bool rk4, RegShape reg,
                            hipStream_t stream);
-// Dynamic LDS a kernel may use without asking, and the request for more (made when a batch's
-// launch shape is set, not for every instantiation when a context is created: that took 2 ms).
+// Dynamic LDS a kernel may use without asking, and the requests for more (made when a batch's
+// launch shape is set, or for its env step, not for every instantiation when a context is
+// created: that took 2 ms).  A kernel's limit is shared by all batches: ask for the device's, not
+// for one batch's need, which would lower it under another's.
 constexpr size_t kDefaultLds = 65536;
 hipError_t allow_step_reg_lds(RegShape reg, bool rk4, size_t bytes);
+hipError_t allow_env_reg_lds(bool dr, size_t bytes);
 // Allow the step kernel `bytes` of dynamic LDS per work-group.
 hipError_t set_step_lds_limit(size_t bytes);
 // Compute body_invweight of a freshly uploaded model (one work-group).

@@ -57,12 +57,6 @@ hipError_t launch_step_reg(const DevGroup* groups, const DevTask* tasks, int nta
 hipError_t launch_env_reg(const DevGroup* groups, const DevTask* tasks, int ntask,
                           const EnvArgs& E, int block, size_t lds_bytes, int tab_words,
                           int ap_words, hipStream_t stream) {
-  if (lds_bytes > kDefaultLds) {
-    const hipError_t e = hipFuncSetAttribute(
-        E.dr ? (const void*)mjh_env_reg_kernel<true> : (const void*)mjh_env_reg_kernel<false>,
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-    if (e != hipSuccess) return e;
-  }
   if (E.dr)
     hipLaunchKernelGGL((mjh_env_reg_kernel<true>), dim3(ntask), dim3(block), lds_bytes, stream,
                        groups, tasks, E, tab_words, ap_words);
@@ -70,6 +64,12 @@ hipError_t launch_env_reg(const DevGroup* groups, const DevTask* tasks, int ntas
     hipLaunchKernelGGL((mjh_env_reg_kernel<false>), dim3(ntask), dim3(block), lds_bytes, stream,
                        groups, tasks, E, tab_words, ap_words);
   return hipGetLastError();
+}
+
+hipError_t allow_env_reg_lds(bool dr, size_t bytes) {
+  return hipFuncSetAttribute(
+      dr ? (const void*)mjh_env_reg_kernel<true> : (const void*)mjh_env_reg_kernel<false>,
+      hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
 hipError_t allow_step_reg_lds(RegShape reg, bool rk4, size_t bytes) {
