@@ -788,6 +788,27 @@ static int worlds_per_block(const mjh_ctx* ctx, const ModelRec& mr, int team, in
   return wpb;
 }
 
+// Register-resident solves where every group with worlds has them: one shape, or a mix of the
+// shapes that the mixed kernel holds; else the solves in LDS for all (nb = 0).
+static RegShape batch_shape(const mjh_batch* b) {
+  RegShape shape;
+  bool first = true, same = true, mix = true;
+  for (const GroupRec& gr : b->groups) {
+    if (gr.nworld == 0) continue;
+    const DevModel& d = b->ctx->models[gr.model]->dm;
+    const RegShape r = reg_shape(d, gr.team);
+    mix = mix && mix_shape(r) && !d.rk4;
+    same = same && (first || (r.team == shape.team && r.nb == shape.nb));
+    if (first) shape = r;
+    first = false;
+  }
+  if (!same) {
+    shape = RegShape();
+    if (mix) shape.nb = 28;
+  }
+  return shape;
+}
+
 // the kernel's view of every group: model tables, bound pointers, counts, team
 static std::vector<DevGroup> group_table(const mjh_batch* b) {
   const mjh_ctx* ctx = b->ctx;
@@ -865,22 +886,7 @@ static mjh_status sync_tables(mjh_batch* b) {
     if (gr.nworld > 0 && ctx->models[gr.model]->dm.rk4) b->rk4 = true;
     if (gr.nworld > 0 && ctx->models[gr.model]->dm.cone) b->cone = true;
   }
-  // register-resident solves where every group has them: one shape, or a mix of the shapes
-  // that the mixed kernel holds
-  b->reg = RegShape();
-  bool first = true, same = true, mix = !b->rk4;
-  for (const GroupRec& gr : b->groups) {
-    if (gr.nworld == 0) continue;
-    const RegShape r = reg_shape(ctx->models[gr.model]->dm, gr.team);
-    mix = mix && mix_shape(r);
-    same = same && (first || (r.team == b->reg.team && r.nb == b->reg.nb));
-    if (first) b->reg = r;
-    first = false;
-  }
-  if (!same) {
-    b->reg = RegShape();
-    if (mix) b->reg.nb = 28;
-  }
+  b->reg = batch_shape(b);
   if (b->reg.nb) {
     b->block = (b->block + 63) & ~63;  // whole wavefronts (team_of)
     if (lds > kDefaultLds) MJH_HIP(allow_step_reg_lds(b->reg, b->rk4, ctx->lds_limit));
@@ -1023,17 +1029,25 @@ mjh_status mjh_world_alloc(mjh_ctx* ctx, const int32_t* model_ids, const int32_t
     const DevModel& d = ctx->models[gr.model]->dm;
     // default launch shape: small trees take a quarter or half of a wavefront, large
     // ones a whole one.  A whole-wavefront world is its own work-group, so the LDS of a
-    // CU can be filled one world at a time.  Smaller teams: in a batch of several models every
-    // work-group gets the largest one's threads and LDS, so groups are one wavefront (4096 mixed
-    // worlds x 2 steps 251 us, against 273 with two and 388 with four).  Alone, with at most two
-    // wavefronts a SIMD, work-groups of four put one on each SIMD of a CU (groups of two can land
-    // on the same two: 1999 worlds x 2 Runge-Kutta steps 506 against 454 us); beyond that groups
-    // of two fill a CU's LDS better (8192 worlds x 3 steps 322 against 325 us, the env step 338
-    // against 362).
+    // CU can be filled one world at a time.
     gr.team = d.nv <= 8 ? 16 : (d.nrowmax <= 32 ? 32 : 64);
-    gr.block = gr.team == 64 || nmodel > 1 ? 64 : 128;
-    if (gr.team == 32 && nmodel == 1 && gr.nworld <= 16 * ctx->num_cu) gr.block = 256;
+    gr.block = gr.team == 64 ? 64 : 128;
     b->groups.push_back(gr);
+  }
+  // Smaller teams on the register-resident solves: in a batch of several models every
+  // work-group gets the largest one's threads and LDS, so groups are one wavefront (4096 mixed
+  // worlds x 2 steps 251 us, against 273 with two and 388 with four).  Alone, with at most two
+  // wavefronts a SIMD, work-groups of four put one on each SIMD of a CU (groups of two can land
+  // on the same two: 1999 worlds x 2 Runge-Kutta steps 506 against 454 us); beyond that groups
+  // of two fill a CU's LDS better (8192 worlds x 3 steps 322 against 325 us, the env step 338
+  // against 362).
+  if (batch_shape(b).nb) {
+    int nactive = 0;
+    for (const GroupRec& gr : b->groups) nactive += gr.nworld > 0;
+    for (GroupRec& gr : b->groups) {
+      if (nactive > 1) gr.block = 64;
+      else if (gr.team == 32 && gr.nworld <= 16 * ctx->num_cu) gr.block = 256;
+    }
   }
   *out = b;
   return MJH_OK;
