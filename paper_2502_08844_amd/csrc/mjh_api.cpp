@@ -750,6 +750,7 @@ struct mjh_batch {
   DevTask* d_tasks = nullptr;
   int ntask = 0;
   int block = 64;
+  int block_worlds = 1;  // worlds of the largest work-group
   int tab_words = 0;
   size_t lds_bytes = 0;
   bool rk4 = false;  // some group integrates by fourth-order Runge-Kutta
@@ -843,7 +844,7 @@ static mjh_status sync_tables(mjh_batch* b) {
   const std::vector<DevGroup> dg = group_table(b);
   struct Tk { DevTask t; double cost; };
   std::vector<Tk> tasks;
-  int block = 0;
+  int block = 0, worlds = 1;
   size_t lds = 0;
   int tab_words = 0;
   for (const GroupRec& gr : b->groups)
@@ -858,6 +859,7 @@ static mjh_status sync_tables(mjh_batch* b) {
     if (tab + per > ctx->lds_limit)
       return fail(ctx, MJH_EUNSUPPORTED, "one world's working set exceeds the LDS limit");
     block = std::max(block, wpb * gr.team);
+    worlds = std::max(worlds, wpb);
     lds = std::max(lds, tab + (size_t)wpb * per);
     for (int w0 = 0; w0 < gr.nworld; w0 += wpb) {
       Tk t;
@@ -879,6 +881,7 @@ static mjh_status sync_tables(mjh_batch* b) {
   b->ntask = (int)dt.size();
   b->tab_words = tab_words;
   b->block = std::max(block, 16);
+  b->block_worlds = worlds;
   b->lds_bytes = lds;
   b->rk4 = false;
   b->cone = false;
@@ -1038,15 +1041,18 @@ mjh_status mjh_world_alloc(mjh_ctx* ctx, const int32_t* model_ids, const int32_t
   // work-group gets the largest one's threads and LDS, so groups are one wavefront (4096 mixed
   // worlds x 2 steps 251 us, against 273 with two and 388 with four).  Alone, with at most two
   // wavefronts a SIMD, work-groups of four put one on each SIMD of a CU (groups of two can land
-  // on the same two: 1999 worlds x 2 Runge-Kutta steps 506 against 454 us); beyond that groups
-  // of two fill a CU's LDS better (8192 worlds x 3 steps 322 against 325 us, the env step 338
-  // against 362).
+  // on the same two: 1999 worlds x 2 Runge-Kutta steps 506 against 454 us), where eight worlds
+  // and the env step's words for them fit; beyond that groups of two fill a CU's LDS better (8192
+  // worlds x 3 steps 322 against 325 us, the env step 338 against 362).
   if (batch_shape(b).nb) {
     int nactive = 0;
     for (const GroupRec& gr : b->groups) nactive += gr.nworld > 0;
     for (GroupRec& gr : b->groups) {
+      const DevModel& d = ctx->models[gr.model]->dm;
+      const size_t words = table_words(d) + 8 * ((size_t)d.lds_words + 3 * d.nu + 8);
       if (nactive > 1) gr.block = 64;
-      else if (gr.team == 32 && gr.nworld <= 16 * ctx->num_cu) gr.block = 256;
+      else if (gr.team == 32 && gr.nworld <= 16 * ctx->num_cu && 4 * words <= ctx->lds_limit)
+        gr.block = 256;
     }
   }
   *out = b;
@@ -1149,9 +1155,8 @@ mjh_status mjh_env_step(mjh_batch* b, int32_t nenv, int32_t nsub, const float* a
   if (st != MJH_OK) return st;
   st = sync_tables(b);
   if (st != MJH_OK) return st;
-  const int teams = std::max(1, b->block / g.team);
   const int ndr = params ? 8 + 2 * h.nu : 0;
-  const int ap_words = (teams * (h.nu + ndr) + 3) & ~3;
+  const int ap_words = (b->block_worlds * (h.nu + ndr) + 3) & ~3;
   const size_t lds = b->lds_bytes + (size_t)ap_words * sizeof(float);
   if (lds > ctx->lds_limit)
     return fail(ctx, MJH_EUNSUPPORTED, "env_step: work-group exceeds the LDS limit");

@@ -17,8 +17,9 @@ def lib():
     return gpu_ctx()
 
 
-def _many_legs(n, ncon):
-    """A free box with n one-hinge legs with position actuators, ncon of them with a foot."""
+def _many_legs(n, ncon, fixed=0):
+    """A free box with n one-hinge legs with position actuators, ncon of them with a foot, and
+    `fixed` bodies without joints."""
     b = robots._Builder("many_legs")
     floor = b.geom(0, GEOM_PLANE, (0, 0, 0))
     root = b.body(0, pos=(0, 0, 1))
@@ -29,6 +30,8 @@ def _many_legs(n, ncon):
         leg = b.body(root, pos=(0.1, 0.05 * i, 0))
         hinges.append(b.joint(leg, JNT_HINGE, axis=(0, 1, 0)))
         feet.append(b.geom(leg, GEOM_SPHERE, (0.05,), pos=(0, 0, -0.2), mass=0.3))
+    for i in range(fixed):
+        b.geom(b.body(root, pos=(-0.1, 0, 0.01 * i)), GEOM_BOX, (0.01, 0.01, 0.01), mass=0.01)
     m = b.finish()
     m.actuators = [Actuator(type=ACT_PD, joint=j, gear=1.0, kp=20.0, kd=0.5, ctrlrange=(-1.0, 1.0),
                             qdefault=0.0) for j in hinges]
@@ -43,9 +46,23 @@ def _many_legs(n, ncon):
 def test_env_step_fits_beside_the_default_worlds(lib, legs, ncon, randomised):
     """Worlds of 20 to 23 KB: as many as 256 threads hold fill the LDS to the last few hundred
     bytes, and the env step needs words of its own."""
+    _env_step(*lib, _many_legs(legs, ncon), randomised)
+
+
+def test_env_step_fits_on_the_register_solves(lib):
+    """20 dofs and 97 bodies without joints: eight worlds of 20,300 bytes fit in 160 KB, but not
+    with the words that randomised worlds need in the env step."""
     mjh, ctx = lib
-    m, nw = _many_legs(legs, ncon), 17
-    print(f"[gpu] env step, {legs} legs, {ncon} feet, randomised {randomised}", flush=True)
+    m = _many_legs(14, 6, 97)
+    d = ctx.model_upload(m).dims
+    room = 160 * 1024 - (d.nv * (d.nv + 1) // 2 + 15) // 16 * 16 - 8 * d.lds_bytes
+    assert 0 <= room < 4 * 8 * (3 * m.nu + 8)
+    _env_step(mjh, ctx, m, True)
+
+
+def _env_step(mjh, ctx, m, randomised):
+    nw = 17
+    print(f"[gpu] env step, {m.nu} legs, randomised {randomised}", flush=True)
     w = mjh.World(ctx, m, nw, qpos=np.tile(m.qpos0, (nw, 1)))
     z = lambda *s: torch.zeros(*s, device="cuda")  # noqa: E731
     params = None
