@@ -163,13 +163,18 @@ struct SweepBase {
   DEV static float solve(Acc& S, const Team& t, int nv, int i, float b, float* A, float& scale,
                          bool& ok) {
     const float e31 = i == 31 ? 1.f : 0.f;
-    S.add_rhs(b, e31);
+    // (an entry that is not finite, times e31's zeros, would spread from the right-hand side into
+    // the matrix, whose pivots say whether it is positive definite: it stays out, and the
+    // solution's entry is no number, which ends the solve at the descent test)
+    const bool finite = fabsf(b) < INFINITY;
+    S.add_rhs(finite ? b : 0.f, e31);
     float pd = 1.f;
     pivot<NB - 1>(S, nv, i, pd);
     ok = !team_any<T>(!(pd > 0.f), t.lane);
     scale = i < nv ? __builtin_amdgcn_rcpf(pd) : 0.f;  // (lane 31 holds the right-hand side)
     S.rows(A);
-    return scale * S.template row<31>();
+    const float x = scale * S.template row<31>();
+    return finite ? x : NAN;
   }
 };
 template <int NB>
