@@ -2797,22 +2797,6 @@ DEV void integrate(const DevModel& m, float* W, const Team& t, int& status) {
 namespace mjh {
 
 // ------------------------------------------------------------- one full step
-// Phase timing for profiling builds only (-DMJH_PHASE_TIMING): every lane accumulates
-// cycle counts per phase; release builds compile the marks away.
-#ifdef MJH_PHASE_TIMING
-#define MJH_MARK(k)                                           \
-  do {                                                        \
-    t.sync();                                                 \
-    long long now_ = (long long)__builtin_readcyclecounter(); \
-    if (ph) ph[k] += now_ - *last;                            \
-    *last = now_;                                             \
-  } while (0)
-#else
-#define MJH_MARK(k) \
-  do {              \
-  } while (0)
-#endif
-
 // Implicit damping (integrator 1): the forces linear in a dof's own velocity (joint
 // damping, PD velocity gains) act at the end-of-step velocity, so the integrator's
 // acceleration solves (M + h diag(b + kd)) a_int = qfrc_smooth + J^T f, with the row
@@ -2865,8 +2849,7 @@ DEV void implicit_damping(const DevModel& m, float* W, const Team& t) {
 // solves in LDS, any team size and model)
 template <bool CONE = false, int TT = 0, int NB = 0>
 DEV void world_step(const DevModel& m, float* W0, const Team& t0, const float* ctrl,
-                    int& status, int iters, float gtol = 0.f, long long* ph = nullptr,
-                    long long* last = nullptr, const float* dr = nullptr) {
+                    int& status, int iters, float gtol = 0.f, const float* dr = nullptr) {
 #define MJH_PHASE_CTX                                   \
   float* W = W0 + opaque_zero();                        \
   const Team t{t0.lane + opaque_zero(), TT ? TT : t0.T, t0.tp};
@@ -2875,22 +2858,18 @@ DEV void world_step(const DevModel& m, float* W0, const Team& t0, const float* c
   if (NB > 0 && m.lane_sweep && m.nbody - 1 <= t0.T) {
     MJH_PHASE_CTX
     sweeps_lanes(m, W, t, ctrl, dr);
-    MJH_MARK(2);
   } else {
   {
     MJH_PHASE_CTX
     actuation(m, W, t, ctrl, dr);
-    MJH_MARK(0);
   }
   {
     MJH_PHASE_CTX
     forward_sweep(m, W, t, nullptr, dr);
-    MJH_MARK(1);
   }
   {
     MJH_PHASE_CTX
     backward_and_mass(m, W, t, dr);
-    MJH_MARK(2);
   }
   }
   // a model that can have no constraint row: the smooth solve ends its step (64 cartpoles, a
@@ -2934,19 +2913,16 @@ DEV void world_step(const DevModel& m, float* W0, const Team& t0, const float* c
       ltdl_factor(m, W, t, W + m.o_a0);  // also solves L^T y = frc in place
       ltdl_solve(m, W, t, nullptr, W + m.o_a0, true);
     }
-    MJH_MARK(3);
   }
   if (rows) {
   {
     MJH_PHASE_CTX
     collide_candidates(m, W, t);
     select_contacts<(NB > 0)>(m, W, t, status, dr);
-    MJH_MARK(4);
   }
   {
     MJH_PHASE_CTX
     constraint_rows<(NB > 0)>(m, W, t);
-    MJH_MARK(5);
   }
   {
     MJH_PHASE_CTX
@@ -2956,7 +2932,6 @@ DEV void world_step(const DevModel& m, float* W0, const Team& t0, const float* c
     } else {
       newton<CONE>(m, W, t, status, iters, gtol);
     }
-    MJH_MARK(6);
   }
   }
   if (m.implicit) {

@@ -9,12 +9,6 @@
 
 namespace mjh {
 
-#ifdef MJH_PHASE_TIMING
-// per-world phase cycle totals of the last launch (profiling builds only)
-constexpr int kPhaseWorlds = 8192;
-static __device__ long long g_phase_cycles[kPhaseWorlds * 8];
-#endif
-
 // RK: the instantiation that can run fourth-order Runge-Kutta groups (four forward
 // passes a step); the other compiles the one-pass step alone.  CONE: the one that can
 // solve elliptic-cone models (with RK, for any batch that has one).
@@ -35,20 +29,12 @@ __device__ __forceinline__ void run_worlds(const DevGroup& G, float* W, int worl
   }
   t.sync();
   int status = 0;
-#ifdef MJH_PHASE_TIMING
-  long long ph[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  long long last = (long long)__builtin_readcyclecounter();
-#endif
   for (int s = 0; s < nstep; s++) {
     const float* u = G.ctrl ? G.ctrl + ((size_t)s * G.nworld + w) * nu : nullptr;
     const bool rk = RK && m.rk4;
     for (int k = 0; k < (rk ? 4 : 1); k++) {
       if (k > 0) rk4_begin(m, W, t, k);
-#ifdef MJH_PHASE_TIMING
-      world_step<CONE, TT, NB>(m, W, t, u, status, m.iterations, 0.f, ph, &last);
-#else
       world_step<CONE, TT, NB>(m, W, t, u, status, m.iterations);
-#endif
       if (k == 0 && s == nstep - 1 && G.con_out)
         export_contacts(m, W, t, G.con_out + w * m.nconmax * kConOut,
                         G.ncon_out ? G.ncon_out + w : nullptr);
@@ -56,17 +42,7 @@ __device__ __forceinline__ void run_worlds(const DevGroup& G, float* W, int worl
     }
     if (rk) rk4_combine(m, W, t, status);
     else integrate(m, W, t, status);
-#ifdef MJH_PHASE_TIMING
-    t.sync();
-    const long long now_ = (long long)__builtin_readcyclecounter();
-    ph[7] += now_ - last;
-    last = now_;
-#endif
   }
-#ifdef MJH_PHASE_TIMING
-  if (lane == 0 && world < kPhaseWorlds)
-    for (int k = 0; k < 8; k++) g_phase_cycles[world * 8 + k] = ph[k];
-#endif
   for (int i = lane; i < nq; i += T) G.qpos[w * nq + i] = W[m.o_qpos + i];
   for (int i = lane; i < nv; i += T) {
     G.qvel[w * nv + i] = W[m.o_qvel + i];
@@ -128,7 +104,7 @@ __device__ __forceinline__ void env_worlds(const DevGroup& G, const EnvArgs& E, 
       const bool rk = RK && m.rk4;
       for (int k = 0; k < (rk ? 4 : 1); k++) {
         if (k > 0) rk4_begin(m, W, t, k);
-        world_step<false, TT, NB>(m, W, t, u, status, m.iterations, 0.f, nullptr, nullptr, dr);
+        world_step<false, TT, NB>(m, W, t, u, status, m.iterations, 0.f, dr);
         if (rk) rk4_accumulate(m, W, t, k);
       }
       if (rk) rk4_combine(m, W, t, status);
