@@ -21,8 +21,10 @@ struct RegShape {
 // The shape for worlds of this model on `team` lanes; nb = 0 where the solves stay in LDS: a
 // world that does not fit its team (16 lanes, more than 16 dofs) or has more than 28 dofs (two
 // matrix rows a lane would not leave the registers of two waves per SIMD), contacts other than
-// condim-3 pyramids (the quad-per-contact layout), and at most 16 dofs on 64 lanes (never a
-// default shape).  Where both run, the registers are 1.9 to 2.6 times faster (mjh_newton_reg.h).
+// condim-3 pyramids (the quad-per-contact layout), and at most 16 dofs on 64 lanes, which has no
+// instantiation and was not measured (by default those are models of 9 to 16 dofs with more than
+// 32 rows).  Where both run, the registers are 1.4 (64 cartpoles: 14.4 against 10.5 us) to 4.2
+// times (1999 quadrupeds by Runge-Kutta: 1297 against 312 us) as fast.
 inline RegShape reg_shape(const DevModel& m, int team) {
   RegShape r;
   if (!m.jframe || m.cone || m.nv < 1 || m.nv > 28) return r;
@@ -32,12 +34,18 @@ inline RegShape reg_shape(const DevModel& m, int team) {
   r.nb = nb;
   return r;
 }
-// Whether a batch of several shapes has a register-resident kernel for this one.
+// Whether a batch of several shapes has a register-resident kernel for this one: the default
+// shapes of the cart-pole, the quadruped, the humanoid and the hand (4096 of the last three x 2
+// steps: 753 us with the solves in LDS, 280 with this kernel).  Every shape that the one kernel
+// holds runs at the registers of its largest (171 VGPRs, two waves a SIMD).  Other shapes and
+// Runge-Kutta were not measured in it; a batch that has one keeps the solves in LDS for all.
 inline bool mix_shape(const RegShape& r) {
   return (r.team == 16 && r.nb == 16) || (r.team == 32 && r.nb == 20) ||
          (r.team == 64 && r.nb == 28);
 }
-// Whether the env step has a register-resident kernel for this shape.
+// Whether the env step has a register-resident kernel for this shape: quadrupeds on 32 lanes
+// (8192 x 4 substeps: 728 us with the solves in LDS, 260 with it).  Other shapes (a quadruped with
+// joint limits and friction loss takes 64 lanes) were not measured and keep the solves in LDS.
 inline bool env_reg_shape(const RegShape& r, bool rk4) { return r.team == 32 && r.nb == 20 && !rk4; }
 
 // Launch the step kernel: one work-group of `block` threads per task; rk4 selects the
